@@ -11,19 +11,24 @@
 //     the boundary token (the kept eligible token with the largest rank).
 //
 // The paper scans q with a Fenwick tree, one dependent tree walk per query. Here
-// every query is answered independently: E(q) is a prefix of the positions s, s+1,
-// ..., so cutoff_q is the k-th smallest value of a prefix of the array
-// A_i = rank_{s+i}, which a wavelet matrix over A answers in ceil(log2 T) constant-
-// time steps. The ranks come from chunks of 4096 positions, each sorted by one
-// workgroup (a stable LSD radix sort of 32-bit priority keys, 8 bits per pass),
-// and then merged: a key's rank is its rank in its own chunk plus, for every other
-// chunk, the number of that chunk's keys ordered before it (a binary search), so
-// a sequence of 32768 positions keeps 8 workgroups busy in each step. One workgroup
-// per sequence then builds the wavelet matrix (one stable partition per bit level,
-// most significant first): in LDS, one scan per level, when A has at most 32767
-// entries and T <= 65536; otherwise in global memory, 1024 consecutive elements per
-// round so that every access is coalesced. Then one thread per query walks the
-// levels.
+// every step is spread over the chip:
+//   1. topk_chunk_sort_kernel: chunks of 4096 positions, each sorted by one workgroup
+//      (a stable LSD radix sort of 32-bit priority keys in LDS, 8 bits per pass).
+//   2. topk_merge_kernel: runs of up to 32 sorted chunks, each workgroup merging the
+//      stretch of every chunk that lies between two sampled keys, about 4096 keys in all.
+//      With one run (T <= 131072) a key's place is its rank.
+//   3. topk_merge_runs_kernel (T > 131072): adds, for each key of a sorted run, the
+//      number of every other run's keys ordered before it.
+//   4. topk_census_kernel: how many eligible tokens of each bucket of consecutive ranks
+//      lie before each block of positions.
+//   5. topk_query_kernel: one workgroup per 1024 consecutive queries. k is fixed and
+//      the eligible set only grows, so while the block's new tokens arrive the cutoff
+//      only walks down from where it stood before the block, past at most one kept
+//      token per arrival. The census gives the bucket that holds the k-th rank before
+//      the block; one scan of it finds that rank; a scan downwards from there lists the
+//      block's candidates (a few thousand at most) in rank order; and each wave then
+//      answers its 64 queries from that list.
+//   6. topk_evict_kernel: each token's first query with a cutoff below its rank.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -36,8 +41,14 @@
 namespace kvpop {
 namespace {
 
-constexpr int kPrepThreads = 1024;
-constexpr int kPrepWaves = kPrepThreads / 64;
+constexpr int kThreads = 1024;
+constexpr int kWaves = kThreads / 64;
+constexpr int kSortJ = 4;                      // elements per thread
+constexpr int kRankChunk = kSortJ * kThreads;  // positions per sorted chunk
+constexpr int kRunChunks = 32;                 // most sorted chunks per run
+constexpr int kRun = kRunChunks * kRankChunk;  // positions per run: 131072
+constexpr int kBlock = 1024;                   // queries per workgroup, ranks per scan step
+constexpr int kMaxBuckets = 1024;              // most rank buckets (and position blocks) of the census
 
 // Monotone map from float to uint32 such that larger floats give larger keys;
 // inverted so that an ascending sort puts the highest priority first. -0.0 and
@@ -58,699 +69,1031 @@ __device__ __forceinline__ float static_priority(float r, float t, float lg) {
 }
 
 // Workgroup barrier after this wave's LDS operations have completed (lgkmcnt(0)),
-// without waiting for its outstanding global stores as __syncthreads() does: for
+// without waiting for its outstanding global accesses as __syncthreads() does: for
 // barriers that only exchange LDS data.
 __device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt and expcnt at their maxima
   asm volatile("s_barrier" ::: "memory");
 }
 
-// Exclusive scan (sum or max) over the 1024 threads of the block. `sh` needs
-// kPrepWaves + 1 ints. Returns the exclusive prefix; `total` gets the reduction.
+// Between a wave's LDS writes and its other lanes' reads of them: a wave's LDS
+// operations complete in order, so only the compiler has to keep them so.
+__device__ __forceinline__ void wave_sync() { asm volatile("" ::: "memory"); }
+
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Inclusive scan over the 64 lanes by DPP: four shifts within rows of 16 lanes, then
+// the last lanes of earlier rows broadcast. `id` is the identity of the operation.
 template <bool MAX>
-__device__ __forceinline__ int block_scan(int v, int* sh, int& total) {
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  int x = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(x, off);
-    if (lane >= off) x = MAX ? max(x, y) : x + y;
-  }
-  if (lane == 63) sh[wid] = x;
-  lds_barrier();
-  if (wid == 0) {
-    int s = lane < kPrepWaves ? sh[lane] : (MAX ? INT32_MIN : 0);
-    int incl = s;
-#pragma unroll
-    for (int off = 1; off < kPrepWaves; off <<= 1) {
-      const int y = __shfl_up(incl, off);
-      if (lane >= off) incl = MAX ? max(incl, y) : incl + y;
-    }
-    if (lane < kPrepWaves) sh[lane] = incl;
-  }
-  lds_barrier();
-  const int before_wave = wid > 0 ? sh[wid - 1] : (MAX ? INT32_MIN : 0);
-  const int prev = __shfl_up(x, 1);  // inclusive value of lane - 1 (all lanes take part)
-  const int excl = MAX ? (lane > 0 ? max(before_wave, prev) : before_wave) : before_wave + x - v;
-  total = sh[kPrepWaves - 1];
-  lds_barrier();
-  return excl;
+__device__ __forceinline__ int wave_scan(int x) {
+  constexpr int id = MAX ? INT32_MIN : 0;
+  auto op = [](int a, int b) { return MAX ? max(a, b) : a + b; };
+  x = op(x, __builtin_amdgcn_update_dpp(id, x, 0x111, 0xF, 0xF, false));  // row_shr:1
+  x = op(x, __builtin_amdgcn_update_dpp(id, x, 0x112, 0xF, 0xF, false));  // row_shr:2
+  x = op(x, __builtin_amdgcn_update_dpp(id, x, 0x114, 0xF, 0xF, false));  // row_shr:4
+  x = op(x, __builtin_amdgcn_update_dpp(id, x, 0x118, 0xF, 0xF, false));  // row_shr:8
+  x = op(x, __builtin_amdgcn_update_dpp(id, x, 0x142, 0xA, 0xF, false));  // row_bcast:15 into rows 1, 3
+  x = op(x, __builtin_amdgcn_update_dpp(id, x, 0x143, 0xC, 0xF, false));  // row_bcast:31 into rows 2, 3
+  return x;
 }
 
-constexpr int kSortJ = 4;  // elements per thread in a sort round
-// Positions per sorted chunk: one sort round of kSortJ x 1024 elements.
-constexpr int kRankChunk = kSortJ * kPrepThreads;
+// Reduction over each row of 16 lanes, the result in all of them.
+template <bool MAX>
+__device__ __forceinline__ int row_reduce(int x) {
+  auto op = [](int a, int b) { return MAX ? max(a, b) : a + b; };
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, false));  // row_ror:8
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x124, 0xF, 0xF, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x122, 0xF, 0xF, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x121, 0xF, 0xF, false));
+  return x;
+}
 
-// LDS of the chunk sort.
-// A chunk is one round of the sort, so a destination never exceeds kRankChunk and
-// the counts fit 16 bits; that leaves room in LDS for the chunk itself.
-struct SortSmem {
-  uint16_t cnt[kSortJ][kPrepWaves][256];  // per-(slot, wave) digit counts of a round (cleared after use)
-  uint16_t pre[kSortJ][kPrepWaves][256];  // destinations: bucket base plus earlier (slot, wave)s
-  int base[256];                          // next free slot of each bucket
-  int sh[kPrepWaves + 1];                 // block_scan scratch
-  uint32_t key[2][kRankChunk];            // the chunk's keys and positions, sorted from one
-  uint32_t val[2][kRankChunk];            // buffer into the other by each pass
+// Scratch of the block-wide exchanges below: two sets of per-wave values, used in
+// turn, so that one barrier per exchange suffices (a wave that writes a set has passed
+// the barrier after the last reads of it).
+struct Exchange {
+  int v[2][kWaves];
 };
 
-// Eligible positions whose wavelet levels are built in LDS: the array A and its
-// partition, 16-bit values each (ranks below 65536). One below 2^15, so that a
-// block's zero and one counts, and their sums, pack into the halves of an int.
-constexpr int kLdsLevels = 32767;
-constexpr int kLdsBlocks = (kLdsLevels + 63) / 64;  // 64-position blocks of a level
-constexpr int kLdsPerThread = (kLdsLevels + kPrepThreads - 1) / kPrepThreads;  // 32
-
-// LDS of the wavelet build.
-struct PrepSmem {
-  int sh[kPrepWaves + 1];        // block_scan scratch
-  int wc[2][2][4 * kPrepWaves];  // wavelet rounds: [round parity][zeros, ones][j * 16 + wave]
-  int bitcnt[32];                // elements of A with each bit set
-  int blk[kLdsBlocks];           // LDS levels: (zeros << 16) | ones of each 64-position block
-  int blkpre[kLdsBlocks];        // and their exclusive prefix sums
-};
-
-// One stable counting-sort pass on the 8-bit digit at `shift` (a pass of an LSD
-// radix sort). A round moves 4096 elements: thread tid takes r0 + 1024 j + tid for
-// j = 0..3, each placed at base[d] + (elements of digit d in earlier (j, wave)
-// pairs of the round) + (earlier lanes of its wave with digit d), the last found
-// with eight ballots. n <= kRankChunk (one round; the 16-bit destinations hold it).
-__device__ __forceinline__ void sort_pass(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                          uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, int n, int shift,
-                                          SortSmem& sm) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid < 256) sm.base[tid] = 0;
-  __syncthreads();
-  for (int i = tid; i < n; i += kPrepThreads) atomicAdd(&sm.base[(kin[i] >> shift) & 255u], 1);
-  __syncthreads();
-  int tot;
-  const int ex = block_scan<false>(tid < 256 ? sm.base[tid] : 0, sm.sh, tot);
-  if (tid < 256) sm.base[tid] = ex;
-  __syncthreads();
-  const uint64_t lt = (1ull << lane) - 1ull;
-  for (int r0 = 0; r0 < n; r0 += kSortJ * kPrepThreads) {
-    uint32_t k[kSortJ], v[kSortJ];
-    int d[kSortJ], rk[kSortJ];
-    bool valid[kSortJ];
-#pragma unroll
-    for (int j = 0; j < kSortJ; ++j) {
-      const int i = r0 + 1024 * j + tid;
-      valid[j] = i < n;
-      k[j] = valid[j] ? kin[i] : 0u;
-      v[j] = valid[j] ? vin[i] : 0u;
-    }
-#pragma unroll
-    for (int j = 0; j < kSortJ; ++j) {
-      d[j] = (int)((k[j] >> shift) & 255u);
-      uint64_t mm = __builtin_amdgcn_ballot_w64(valid[j]);
-#pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const bool bit = (d[j] >> b) & 1;
-        const uint64_t bb = __builtin_amdgcn_ballot_w64(bit);
-        mm &= bit ? bb : ~bb;
-      }
-      rk[j] = __popcll(mm & lt);
-      if (valid[j] && rk[j] == 0) sm.cnt[j][wave][d[j]] = (uint16_t)__popcll(mm);
-    }
-    __syncthreads();
-    if (tid < 256) {
-      int run = sm.base[tid];
-#pragma unroll
-      for (int j = 0; j < kSortJ; ++j) {
-        int c[kPrepWaves];
-#pragma unroll
-        for (int w = 0; w < kPrepWaves; ++w) c[w] = sm.cnt[j][w][tid];
-#pragma unroll
-        for (int w = 0; w < kPrepWaves; ++w) {
-          sm.pre[j][w][tid] = (uint16_t)run;
-          sm.cnt[j][w][tid] = 0;
-          run += c[w];
-        }
-      }
-      sm.base[tid] = run;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kSortJ; ++j) {
-      if (valid[j]) {
-        const int dst = sm.pre[j][wave][d[j]] + rk[j];
-        kout[dst] = k[j];
-        vout[dst] = v[j];
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// One wavelet-matrix level: stable partition of ain by bit `bit` (zeros first) into
-// aout, and the level's bit words bw[W + 1] and ones-before-word counts cw[W + 1].
-// A round covers 4096 elements: thread tid takes r0 + 1024 j + tid for j = 0..3, so
-// each (j, wave) ballot is 64 consecutive bits, i.e. two words of the level; the
-// zeros and ones before each (j, wave) come from one exchange of the 64 counts and a
-// scan across the lanes of every wave.
-// total_ones: elements with bit `bit` set (a reordering does not change it).
-__device__ __forceinline__ uint32_t wavelet_level(const uint32_t* __restrict__ ain, uint32_t* __restrict__ aout,
-                                                  int n, int bit, int total_ones, uint32_t* __restrict__ bw,
-                                                  uint32_t* __restrict__ cw, PrepSmem& sm) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int W = (n + 31) / 32;
-  const uint64_t lt = (1ull << lane) - 1ull;
-  int zrun = 0, orun = n - total_ones;  // next slots of zeros and ones
-  int onesb = 0;                        // ones before this round
-  for (int r0 = 0, par = 0; r0 < n; r0 += 4 * kPrepThreads, par ^= 1) {
-    uint32_t x[4];
-    bool one[4], valid[4];
-    uint64_t ob[4], zb[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int i = r0 + 1024 * j + tid;
-      valid[j] = i < n;
-      x[j] = valid[j] ? ain[i] : 0u;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      one[j] = valid[j] && ((x[j] >> bit) & 1u);
-      ob[j] = __builtin_amdgcn_ballot_w64(one[j]);
-      zb[j] = __builtin_amdgcn_ballot_w64(valid[j]) & ~ob[j];
-    }
-    int* zc = sm.wc[par][0];  // [j * 16 + wave]
-    int* oc = sm.wc[par][1];
-    if (lane == 0) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        zc[j * kPrepWaves + wave] = __popcll(zb[j]);
-        oc[j * kPrepWaves + wave] = __popcll(ob[j]);
-      }
-    }
-    lds_barrier();
-    // Exclusive scans of the 64 counts in (j, wave) order, one count per lane.
-    int zi = zc[lane], oi = oc[lane];
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int zy = __shfl_up(zi, off), oy = __shfl_up(oi, off);
-      if (lane >= off) {
-        zi += zy;
-        oi += oy;
-      }
-    }
-    const int ztot = __shfl(zi, 63), otot = __shfl(oi, 63);
-    const int zex = zi - zc[lane], oex = oi - oc[lane];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int zpre = __shfl(zex, j * kPrepWaves + wave), opre = __shfl(oex, j * kPrepWaves + wave);
-      if (valid[j]) aout[one[j] ? orun + opre + __popcll(ob[j] & lt) : zrun + zpre + __popcll(zb[j] & lt)] = x[j];
-      const int p0 = r0 + 1024 * j + 64 * wave;
-      if (lane == 0 && p0 < n) {
-        const int wd = p0 >> 5;
-        bw[wd] = (uint32_t)ob[j];
-        cw[wd] = (uint32_t)(onesb + opre);
-        if (wd + 1 < W) {
-          bw[wd + 1] = (uint32_t)(ob[j] >> 32);
-          cw[wd + 1] = (uint32_t)(onesb + opre + __popc((uint32_t)ob[j]));
-        }
-      }
-    }
-    zrun += ztot;
-    orun += otot;
-    onesb += otot;
-  }
-  if (tid == 0) {
-    bw[W] = 0u;
-    cw[W] = (uint32_t)total_ones;
-  }
-  __syncthreads();  // the next level reads aout
-  return (uint32_t)(n - total_ones);
-}
-
-// One wavelet-matrix level for an array of at most kLdsLevels elements in LDS, the
-// same result as wavelet_level. Thread tid holds the elements 1024 e + tid of all 32
-// slots e in registers, so the level needs one scan, over the zero and one counts of
-// its 64-position blocks (block 16 e + wave), instead of one per round: a pass of
-// ballots, the scan, and a pass that scatters the elements. Both passes stop at the
-// last slot that holds elements; within them the loads never branch (the buffers
-// hold 32768 entries; those from n on are ignored). Each wave gathers its 32 block
-// counts, prefixes and 64 bit words in lanes, so that each moves in one instruction.
-__device__ __forceinline__ uint32_t wavelet_level_lds(const uint16_t* __restrict__ ain, uint16_t* __restrict__ aout,
-                                                      int n, int bit, uint32_t* __restrict__ bw,
-                                                      uint32_t* __restrict__ cw, PrepSmem& sm) {
-  constexpr int E = kLdsPerThread;  // 32 slots of 1024 positions
-  static_assert(2 * E == 64, "two bit words per slot fill a wave");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int W = (n + 31) / 32;
-  const uint64_t lt = (1ull << lane) - 1ull;
-  uint32_t x[E];
-  int cntv = 0;  // lane e: (zeros << 16) | ones of slot e's block
-  // An opaque copy of n: the 32 compares against it are then made at every level,
-  // not hoisted out of the level loop as 32 masks that spill.
-  int n1 = n;
-  asm volatile("" : "+s"(n1));
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    if (e * kPrepThreads >= n1) break;  // slots past the array (a scalar branch)
-    const int i = e * kPrepThreads + tid;
-    x[e] = ain[i];
-    const bool valid = i < n1, one = valid && ((x[e] >> bit) & 1u);
-    const uint64_t ob = __builtin_amdgcn_ballot_w64(one);
-    const uint64_t zb = __builtin_amdgcn_ballot_w64(valid) & ~ob;
-    const int packed = (__popcll(zb) << 16) | __popcll(ob);
-    cntv = lane == e ? packed : cntv;
-  }
-  if (lane < E) sm.blk[16 * lane + wave] = cntv;  // blocks past n count nothing
+// Combines one value per wave over the block: `before` gets the reduction over the
+// earlier waves, `total` over all of them. Every thread calls it.
+template <bool MAX>
+__device__ __forceinline__ void wave_totals(int mine, Exchange& ex, int& turn, int& before, int& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int* s = ex.v[turn & 1];
+  ++turn;
+  if (lane == 0) s[wave] = mine;
   lds_barrier();
-  int tot;
-  const int ex = block_scan<false>(tid < kLdsBlocks ? sm.blk[tid] : 0, sm.sh, tot);
-  if (tid < kLdsBlocks) sm.blkpre[tid] = ex;
-  lds_barrier();
-  const int zeros = tot >> 16, ones = tot & 0xFFFF;
-  const int prev = lane < E ? sm.blkpre[16 * lane + wave] : 0;  // lane e: slot e's prefix
-  uint32_t wv = 0u, cv = 0u;  // lane 2 e + h: word h of slot e's block and the ones before it
-  // The ballots are taken again rather than kept: held across the scan, the 64
-  // masks would spill. (Opaque copies of bit and n keep the compiler from reusing
-  // the first pass's masks.)
-  int bit2 = bit, n2 = n;
-  asm volatile("" : "+s"(bit2), "+s"(n2));
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    if (e * kPrepThreads >= n2) break;
-    const int i = e * kPrepThreads + tid;
-    const bool valid = i < n2, one = valid && ((x[e] >> bit2) & 1u);
-    const uint64_t ob = __builtin_amdgcn_ballot_w64(one);
-    const uint64_t zb = __builtin_amdgcn_ballot_w64(valid) & ~ob;
-    const int pre = __builtin_amdgcn_readlane(prev, e);
-    const int zpre = pre >> 16, opre = pre & 0xFFFF;
-    if (valid) aout[one ? zeros + opre + __popcll(ob & lt) : zpre + __popcll(zb & lt)] = (uint16_t)x[e];
-    const uint32_t lo = (uint32_t)ob;
-    wv = lane == 2 * e ? lo : (lane == 2 * e + 1 ? (uint32_t)(ob >> 32) : wv);
-    cv = lane == 2 * e ? (uint32_t)opre : (lane == 2 * e + 1 ? (uint32_t)(opre + __popc(lo)) : cv);
-  }
-  // Lane 2 e + h writes word 2 (16 e + wave) + h; words from W on belong to no block.
-  const int wd = 2 * (16 * (lane >> 1) + wave) + (lane & 1);
-  if (wd < W) {
-    bw[wd] = wv;
-    cw[wd] = cv;
-  }
-  if (tid == 0) {
-    bw[W] = 0u;
-    cw[W] = (uint32_t)ones;
-  }
-  lds_barrier();  // the next level reads aout
-  return (uint32_t)zeros;
+  const int x = s[lane & (kWaves - 1)];
+  total = __builtin_amdgcn_readfirstlane(row_reduce<MAX>(x));
+  before = __builtin_amdgcn_readfirstlane(row_reduce<MAX>((lane & (kWaves - 1)) < wave ? x : (MAX ? INT32_MIN : 0)));
 }
 
+// Threads before this one (in thread order) with the flag set, and the block's total.
+__device__ __forceinline__ int block_count(bool flag, Exchange& ex, int& turn, int& total) {
+  const uint64_t m = __builtin_amdgcn_ballot_w64(flag);
+  int before;
+  wave_totals<false>(__builtin_popcountll(m), ex, turn, before, total);
+  return before + lanes_below(m);
+}
+
+// ---------------------------------------------------------------------------
+// Workspace of one sequence
+// ---------------------------------------------------------------------------
 struct SegWork {
-  uint32_t* ka;
-  uint32_t* kb;
+  uint32_t* ka;      // keys and positions of the sorted chunks
   uint32_t* va;
+  uint32_t* kb;      // and of the sorted runs (T > kRun)
   uint32_t* vb;
-  int32_t* ps;     // positions in rank order
-  int32_t* pmax;   // prefix maximum of A
-  uint32_t* bits;  // [L][W + 1] bit words of each level
-  uint32_t* cnt;   // [L][W + 1] ones before each word
-  uint32_t* zeros; // [L]
+  int32_t* ps;       // positions in rank order
+  uint32_t* census;  // [blocks][buckets], see topk_census_kernel
 };
 
-__device__ __forceinline__ SegWork seg_work(void* ws, size_t per_seg_words, int seg, int T, int L) {
-  uint32_t* base = reinterpret_cast<uint32_t*>(ws) + (size_t)seg * per_seg_words;
-  const size_t W1 = (size_t)(T + 31) / 32 + 1;
+__device__ __forceinline__ SegWork seg_work(void* ws, size_t per_seg_words, int seg, int T) {
   SegWork s;
-  s.ka = base;
+  s.ka = reinterpret_cast<uint32_t*>(ws) + (size_t)seg * per_seg_words;
   s.kb = s.ka + T;
   s.va = s.kb + T;
   s.vb = s.va + T;
   s.ps = reinterpret_cast<int32_t*>(s.vb + T);
-  s.pmax = s.ps + T;
-  s.bits = reinterpret_cast<uint32_t*>(s.pmax + T);
-  s.cnt = s.bits + (size_t)L * W1;
-  s.zeros = s.cnt + (size_t)L * W1;
+  s.census = reinterpret_cast<uint32_t*>(s.ps + T);
   return s;
 }
 
-// One workgroup per (sequence, chunk of kRankChunk positions): the chunk's priority
-// keys and positions, sorted by key in place in ka / va. The sort is stable and the
-// positions enter in order, so equal keys stay in position order.
-// With a single chunk (T <= kRankChunk) the sorted order is the ranking: the kernel
-// then writes rank[t] and the positions in rank order itself, and no merge follows.
-__global__ __launch_bounds__(kPrepThreads) void topk_chunk_sort_kernel(const float* __restrict__ scores,
-                                                                       const float* __restrict__ log_gamma, int H,
-                                                                       int T, int L, void* ws, size_t per_seg_words,
-                                                                       int32_t* __restrict__ rank) {
+// log2 of the ranks per census bucket, and of the positions per block: 10, or more
+// where that would make over kMaxBuckets of them (T > 2^20).
+__host__ __device__ inline int census_shift(int T) {
+  int sh = 10;
+  while (((T - 1) >> sh) >= kMaxBuckets) ++sh;
+  return sh;
+}
+__host__ __device__ inline int census_buckets(int T) { return ((T - 1) >> census_shift(T)) + 1; }
+
+// ---------------------------------------------------------------------------
+// 1. Chunk sort
+// ---------------------------------------------------------------------------
+// LDS of the chunk sort, 76 KB: two workgroups share a CU. Digit d's counters of a
+// (slot, wave) row sit at slot(d) = 64 (d % 4) + d / 4, 16 waves side by side, so that
+// the thread that sums digit 4 lane + e reads and writes whole 16-byte rows next to its
+// neighbour lanes'.
+struct SortSmem {
+  alignas(16) uint8_t cnt[kSortJ][256][kWaves];    // elements of a digit per (slot, wave): at most 64
+  alignas(16) uint16_t dst[kSortJ][256][kWaves];   // where the first of them goes
+  alignas(16) int part[kSortJ][256];               // per digit and slot
+  alignas(16) uint32_t key[kRankChunk];
+  alignas(16) uint16_t idx[kRankChunk];            // position within the chunk
+  int census[kSortJ][kSortJ];
+};
+
+// One stable counting-sort pass on the 8-bit digit at `shift`. Thread tid holds the
+// elements 1024 j + tid, j < 4, before and after. An element goes to (elements with
+// smaller digits) + (elements of its digit in earlier (j, wave) rows) + (earlier lanes
+// of its wave with its digit, found with eight ballots). Bound by vector instructions,
+// about 290 per wave: 7000 cycles per pass, 16.8 us for the whole sort of up to 256 chunks
+// (28-31 us with a histogram by LDS atomics and one thread per digit's 64 counters).
+__device__ __forceinline__ void sort_pass(uint32_t (&k)[kSortJ], uint32_t (&v)[kSortJ], int shift, SortSmem& sm) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int row[kSortJ], rk[kSortJ];
+#pragma unroll
+  for (int j = 0; j < kSortJ; ++j) {
+    const uint32_t d = (k[j] >> shift) & 255u;
+    uint32_t lo = ~0u, hi = ~0u;  // lanes with the same digit
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      uint32_t own = (uint32_t)__builtin_amdgcn_sbfe((int)k[j], shift + b, 1);  // all ones if the bit is set
+      asm("" : "+v"(own));
+      const uint64_t bb = __builtin_amdgcn_ballot_w64((int)own < 0);
+      // lo & ~(bb ^ own), one instruction per half
+      lo = __builtin_amdgcn_bitop3_b32(lo, own, (uint32_t)bb, 0x90);
+      hi = __builtin_amdgcn_bitop3_b32(hi, own, (uint32_t)(bb >> 32), 0x90);
+    }
+    rk[j] = (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+    row[j] = (int)(64u * (d & 3u) + (d >> 2));
+    if (rk[j] == 0) sm.cnt[j][row[j]][wave] = (uint8_t)(__popc(lo) + __popc(hi));
+  }
+  lds_barrier();
+  // Thread (e, g, lane) owns digit 4 lane + e of slot g: e = wave % 4, g = wave / 4.
+  const int e = wave & 3, g = wave >> 2, r = 64 * e + lane;
+  const uint4 c4 = *reinterpret_cast<const uint4*>(&sm.cnt[g][r][0]);
+  *reinterpret_cast<uint4*>(&sm.cnt[g][r][0]) = uint4{0u, 0u, 0u, 0u};  // for the next pass
+  const uint32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
+  uint32_t sum = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) sum = __builtin_amdgcn_sad_u8(c[i], 0u, sum);
+  sm.part[g][4 * lane + e] = (int)sum;
+  lds_barrier();
+  int p[kSortJ][4], tot = 0;
+#pragma unroll
+  for (int i = 0; i < kSortJ; ++i) {
+    const int4 x = *reinterpret_cast<const int4*>(&sm.part[i][4 * lane]);
+    p[i][0] = x.x, p[i][1] = x.y, p[i][2] = x.z, p[i][3] = x.w;
+    tot += x.x + x.y + x.z + x.w;
+  }
+  int at = wave_scan<false>(tot) - tot;  // elements with digits below 4 lane
+#pragma unroll
+  for (int i = 0; i < kSortJ; ++i)
+#pragma unroll
+    for (int f = 0; f < 4; ++f)
+      if (f < e || (f == e && i < g)) at += p[i][f];
+  uint32_t out[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const uint32_t a = (uint32_t)at;
+    at += (int)((c[i >> 1] >> (16 * (i & 1))) & 255u);
+    out[i] = a | ((uint32_t)at << 16);
+    at += (int)((c[i >> 1] >> (16 * (i & 1) + 8)) & 255u);
+  }
+  *reinterpret_cast<uint4*>(&sm.dst[g][r][0]) = uint4{out[0], out[1], out[2], out[3]};
+  *reinterpret_cast<uint4*>(&sm.dst[g][r][8]) = uint4{out[4], out[5], out[6], out[7]};
+  lds_barrier();
+#pragma unroll
+  for (int j = 0; j < kSortJ; ++j) {
+    const int d = (int)sm.dst[j][row[j]][wave] + rk[j];
+    sm.key[d] = k[j];
+    sm.idx[d] = (uint16_t)v[j];
+  }
+  lds_barrier();
+#pragma unroll
+  for (int j = 0; j < kSortJ; ++j) {
+    k[j] = sm.key[j * kThreads + tid];
+    v[j] = sm.idx[j * kThreads + tid];
+  }
+}
+
+// One workgroup per (sequence, chunk of kRankChunk positions). Positions past T sort
+// last: they have the largest key and enter last. With a single chunk the sorted order
+// is the ranking: the kernel then writes the ranks, the positions in rank order and the
+// census itself.
+__global__ __launch_bounds__(kThreads) void topk_chunk_sort_kernel(const float* __restrict__ scores,
+                                                                   const float* __restrict__ log_gamma, int nseg, int H,
+                                                                   int T, int s, void* ws, size_t per_seg_words,
+                                                                   int32_t* __restrict__ rank) {
   __shared__ SortSmem sm;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int nch = (T + kRankChunk - 1) / kRankChunk;
-  const int seg = (int)blockIdx.x / nch, c = (int)blockIdx.x - seg * nch;
-  const int h = seg % H;
-  SegWork w = seg_work(ws, per_seg_words, seg, T, L);
-  const float lg = log_gamma ? log_gamma[h] : 0.f;
+  const int c = (int)blockIdx.x / nseg, seg = (int)blockIdx.x - c * nseg;
+  SegWork w = seg_work(ws, per_seg_words, seg, T);
+  const float lg = log_gamma ? log_gamma[seg % H] : 0.f;
   const float* r = scores + (size_t)seg * T;
   const int t0 = c * kRankChunk, n = min(kRankChunk, T - t0);
 
-  for (int i = tid; i < kSortJ * kPrepWaves * 256; i += kPrepThreads) (&sm.cnt[0][0][0])[i] = 0;
-  // Keys and positions into LDS; no fma contraction, to match fl(r - fl(t * lg)).
-  for (int i = tid; i < n; i += kPrepThreads) {
-    const int t = t0 + i;
-    sm.key[0][i] = desc_key(static_priority(r[t], (float)t, lg));
-    sm.val[0][i] = (uint32_t)t;
+  uint32_t k[kSortJ], v[kSortJ];
+  float x[kSortJ];
+#pragma unroll
+  for (int j = 0; j < kSortJ; ++j) x[j] = r[min(t0 + j * kThreads + tid, T - 1)];
+#pragma unroll
+  for (int j = 0; j < kSortJ; ++j) {
+    const int i = j * kThreads + tid;
+    asm volatile("" : "+v"(x[j]));  // the loads stay together, not each in a branch of its own
+    k[j] = i < n ? desc_key(static_priority(x[j], (float)(t0 + i), lg)) : ~0u;
+    v[j] = (uint32_t)i;
   }
-  __syncthreads();
-  sort_pass(sm.key[0], sm.val[0], sm.key[1], sm.val[1], n, 0, sm);
-  sort_pass(sm.key[1], sm.val[1], sm.key[0], sm.val[0], n, 8, sm);
-  sort_pass(sm.key[0], sm.val[0], sm.key[1], sm.val[1], n, 16, sm);
-  sort_pass(sm.key[1], sm.val[1], sm.key[0], sm.val[0], n, 24, sm);
-  if (nch == 1) {
-    for (int i = tid; i < n; i += kPrepThreads) {
-      const int t = (int)sm.val[0][i];
-      rank[(size_t)seg * T + t] = i;
-      w.ps[i] = t;
+  reinterpret_cast<uint4*>(sm.cnt)[tid] = uint4{0u, 0u, 0u, 0u};
+  if (tid < kSortJ * kSortJ) (&sm.census[0][0])[tid] = 0;
+  lds_barrier();
+  sort_pass(k, v, 0, sm);
+  sort_pass(k, v, 8, sm);
+  sort_pass(k, v, 16, sm);
+  sort_pass(k, v, 24, sm);
+  if (nch > 1) {
+#pragma unroll
+    for (int j = 0; j < kSortJ; ++j) {
+      const int i = j * kThreads + tid;
+      if (i < n) {
+        w.ka[t0 + i] = k[j];
+        w.va[t0 + i] = (uint32_t)t0 + v[j];
+      }
     }
     return;
   }
-  for (int i = tid; i < n; i += kPrepThreads) {
-    w.ka[t0 + i] = sm.key[0][i];
-    w.va[t0 + i] = sm.val[0][i];
+  // census[block][bucket], see topk_census_kernel: slot j holds bucket j's ranks.
+#pragma unroll
+  for (int j = 0; j < kSortJ; ++j) {
+    const int i = j * kThreads + tid, t = (int)v[j];
+    if (i < n) {
+      rank[(size_t)seg * T + t] = i;
+      w.ps[i] = t;
+    }
+#pragma unroll
+    for (int b = 1; b < kSortJ; ++b) {
+      const int cb = __builtin_popcountll(__builtin_amdgcn_ballot_w64(i < n && t >= s && t < b * kBlock));
+      if (lane == 0 && cb) atomicAdd(&sm.census[b][j], cb);
+    }
+  }
+  lds_barrier();
+  const int nb = census_buckets(T);
+  if (tid < kSortJ * kSortJ) {
+    const int blk = tid / kSortJ, b = tid - blk * kSortJ;
+    if (blk < nb && b < nb) w.census[blk * nb + b] = (uint32_t)sm.census[blk][b];
   }
 }
 
-// For each key, the number of keys of a sorted chunk (m of them) ordered before it:
-// those below it, and with LE (an earlier chunk) those equal to it too. The kSortJ
-// searches advance together, so that their LDS reads overlap, and never branch.
+// ---------------------------------------------------------------------------
+// 2, 3. Merges
+// ---------------------------------------------------------------------------
+// For four ascending keys, the number of entries of the sorted array B[0, len) in LDS
+// ordered before each: those below it, and with LE (entries of earlier positions) those
+// equal to it too. The first key is searched over the whole array; the others only up
+// to the next thread's first key, a few entries away. near: LDS for the first keys'
+// results. Every thread of the block calls it.
 template <bool LE>
-__device__ __forceinline__ void count_before(const uint32_t* __restrict__ sorted, int m,
-                                             const uint32_t (&key)[kSortJ], int (&rk)[kSortJ]) {
-  int pos[kSortJ];
+__device__ __forceinline__ void count_before(const uint32_t* __restrict__ B, int len,
+                                             const uint32_t (&key)[kSortJ], int (&at)[kSortJ], int* near) {
+  const int tid = threadIdx.x;
+  auto before = [&](uint32_t x, uint32_t y) { return LE ? x <= y : x < y; };
+  int lo = 0;
+  for (int step = len > 0 ? 1 << (31 - __builtin_clz(len)) : 0; step > 0; step >>= 1) {
+    const int np = lo + step;
+    lo = np <= len && before(B[min(np, len) - 1], key[0]) ? np : lo;
+  }
+  near[tid] = lo;
+  lds_barrier();
+  const int hi = tid + 1 < kThreads ? near[tid + 1] : len;
+  at[0] = lo;
+  int l[kSortJ], m[kSortJ];
 #pragma unroll
-  for (int j = 0; j < kSortJ; ++j) pos[j] = 0;
+  for (int j = 1; j < kSortJ; ++j) {
+    l[j] = lo;
+    m[j] = hi - lo;
+  }
+  while (__builtin_amdgcn_ballot_w64((m[1] | m[2] | m[3]) > 0) != 0) {
 #pragma unroll
-  for (int step = kRankChunk; step > 0; step >>= 1) {
-#pragma unroll
-    for (int j = 0; j < kSortJ; ++j) {
-      const int np = pos[j] + step;
-      const uint32_t x = sorted[min(np, m) - 1];
-      const bool before = LE ? x <= key[j] : x < key[j];
-      pos[j] = ((np <= m) & before) ? np : pos[j];
+    for (int j = 1; j < kSortJ; ++j) {
+      const int half = m[j] >> 1;
+      const bool some = m[j] > 0;
+      const bool b = some && before(B[some ? l[j] + half : 0], key[j]);
+      l[j] = b ? l[j] + half + 1 : l[j];
+      m[j] = b ? m[j] - half - 1 : half;
     }
   }
 #pragma unroll
-  for (int j = 0; j < kSortJ; ++j) rk[j] += pos[j];
+  for (int j = 1; j < kSortJ; ++j) at[j] = l[j];
+  lds_barrier();  // near is free again
 }
 
-// One workgroup per (sequence, chunk): the rank of each of the chunk's keys (the
-// descending priority order, ties to the earlier position) is its index in the
-// sorted chunk plus, for every other chunk, the number of that chunk's keys ordered
-// before it. An earlier chunk holds only earlier positions, so its equal keys count;
-// a later chunk's do not. Writes rank[t] and the positions in rank order (ps).
-// Chunks are staged in LDS kMergeGroup at a time, their loads all in flight at once.
-constexpr int kMergeGroup = 8;
-__global__ __launch_bounds__(kPrepThreads) void topk_merge_rank_kernel(int T, int L, void* ws, size_t per_seg_words,
-                                                                       int32_t* __restrict__ rank) {
-  __shared__ uint32_t other[kMergeGroup][kRankChunk];
-  const int tid = threadIdx.x;
+constexpr int kGap = 128;                      // a sample of a sorted chunk is every 128th key
+constexpr int kSamples = kRankChunk / kGap;    // per chunk
+constexpr int kMergeCap = kRankChunk + kRunChunks * kGap;  // keys between two splitters: fewer, see topk_merge_kernel
+
+// Merges neighbouring lists pairwise, in LDS: with n lists at off[i << shift] .. off[(i +
+// 1) << shift], lists 2 i and 2 i + 1 become one, equal keys of list 2 i first. Each
+// thread writes `per` consecutive outputs: it finds where they start in the two lists by
+// a binary search along the merge path, then takes the smaller head each time.
+__device__ __forceinline__ void merge_level(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
+                                            uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, const int* off,
+                                            int shift, int npairs, int total, int per) {
+  int e = (int)threadIdx.x * per;
+  const int end = min(e + per, total);
+  if (e >= end) return;
+  int i = 0;  // the pair that output e belongs to
+  for (int step = npairs >> 1; step > 0; step >>= 1)
+    if (off[(i + step) << (shift + 1)] <= e) i += step;
+  const int a0 = off[i << (shift + 1)];
+  int a1 = off[(2 * i + 1) << shift], b1 = off[(i + 1) << (shift + 1)];
+  const int d = e - a0;
+  int lo = max(0, d - (b1 - a1)), hi = min(d, a1 - a0);
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    const bool first = kin[a0 + mid] <= kin[a1 + d - 1 - mid];
+    lo = first ? mid + 1 : lo;
+    hi = first ? hi : mid;
+  }
+  int a = a0 + lo, b = a1 + d - lo;
+  // Heads of both lists and the keys behind them, so that no step waits for the read it
+  // issues.
+  auto at = [&](int i) __attribute__((always_inline)) { return kin[min(i, total - 1)]; };
+  uint32_t ka = at(a), ka1 = at(a + 1), kb = at(b), kb1 = at(b + 1);
+  for (; e < end; ++e) {
+    while (a == a1 && b == b1) {  // on to the next pair that is not empty
+      ++i;
+      a = b1;
+      a1 = b = off[(2 * i + 1) << shift];
+      b1 = off[(i + 1) << (shift + 1)];
+      ka = at(a), ka1 = at(a + 1), kb = at(b), kb1 = at(b + 1);
+    }
+    const bool first = a < a1 && (b >= b1 || ka <= kb);
+    kout[e] = first ? ka : kb;
+    vout[e] = vin[first ? a : b];
+    a += first ? 1 : 0;
+    b += first ? 0 : 1;
+    const uint32_t next = at((first ? a : b) + 1);
+    ka = first ? ka1 : ka;
+    kb = first ? kb : kb1;
+    ka1 = first ? next : ka1;
+    kb1 = first ? kb1 : next;
+  }
+}
+
+// One workgroup per (sequence, chunk): as many workgroups as chunks share a run's keys
+// evenly. The run's samples (every kGap-th key of each chunk) are merged, in key order with
+// ties to the earlier chunk, and workgroup b of nc takes the keys from the sample b / nc of
+// the way up to the one (b + 1) / nc of the way. That is at most kSamples samples, so at
+// most kRankChunk keys and kGap - 1 more per chunk: under kMergeCap. Where a splitter falls
+// in a chunk is known to within the keys between two samples, which one wave reads. The
+// stretches are gathered in LDS in chunk order and merged pairwise; equal keys keep the
+// chunks' order, so ties go to the earlier position. FINAL (the only run): places are
+// ranks, written with the positions in rank order. Otherwise the run's keys and positions
+// go to its sorted arrays.
+// Bound by the LDS latency of the merge levels (a search and about five outputs per
+// thread and level), then by the scattered writes of the ranks: 20.2 us for 4 x 8 x 32768,
+// 29.0 us for 1 x 8 x 131072 (27 and about 120 us when every key was searched in every
+// other chunk).
+template <bool FINAL>
+__global__ __launch_bounds__(kThreads) void topk_merge_kernel(int nseg, int T, void* ws, size_t per_seg_words,
+                                                                   int32_t* __restrict__ rank) {
+  __shared__ uint32_t key[2][kMergeCap], pos[2][kMergeCap];
+  __shared__ int off[kRunChunks + 1];
+  __shared__ int wlo[2 * kRunChunks], wlen[2 * kRunChunks];  // window of a boundary; its first entry and length
+  __shared__ uint32_t wkey[2 * kRunChunks];
+  __shared__ int bound[2 * kRunChunks];                      // boundaries of chunk c's stretch: 2 c, 2 c + 1
+  __shared__ int totals[2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nch = (T + kRankChunk - 1) / kRankChunk;
-  const int seg = (int)blockIdx.x / nch, c = (int)blockIdx.x - seg * nch;
-  SegWork w = seg_work(ws, per_seg_words, seg, T, L);
-  const int t0 = c * kRankChunk, n = min(kRankChunk, T - t0);
+  const int c0 = (int)blockIdx.x / nseg, seg = (int)blockIdx.x - c0 * nseg;
+  SegWork w = seg_work(ws, per_seg_words, seg, T);
+  const int run = c0 / kRunChunks, b = c0 - run * kRunChunks;
+  const int r0 = run * kRun, n = min(kRun, T - r0);
+  const int nc = (n + kRankChunk - 1) / kRankChunk;
+  int lg = 0;  // lists: a power of two, the last ones empty
+  while ((1 << lg) < nc) ++lg;
+  const int P = 1 << lg;
+  const uint32_t* ka = w.ka + r0;
+  const uint32_t* va = w.va + r0;
+
+  // Samples: [0] keeps them chunk by chunk, the merges alternate between 1 and 2.
+  constexpr int kMost = kRunChunks * kSamples;
+  static_assert(kMost <= kThreads, "one sample per thread");
+  uint32_t(*sk)[kMost] = reinterpret_cast<uint32_t(*)[kMost]>(&key[0][0]);
+  uint32_t(*sv)[kMost] = reinterpret_cast<uint32_t(*)[kMost]>(&pos[0][0]);
+  const int ns = P * kSamples;
+  if (tid < ns) {
+    const int i = tid * kGap;
+    const uint32_t x = ka[min(i, n - 1)];
+    sk[0][tid] = i < n ? x : ~0u;
+    sv[0][tid] = (uint32_t)tid;
+  }
+  if (tid <= P) off[tid] = tid * kSamples;
+  lds_barrier();
+  int cur = 0;
+  for (int l = 0; l < lg; ++l) {
+    const int nxt = cur == 1 ? 2 : 1;
+    merge_level(sk[cur], sv[cur], sk[nxt], sv[nxt], off, l, P >> (l + 1), ns, 1);
+    cur = nxt;
+    lds_barrier();
+  }
+  // Where the two splitters fall in each chunk: thread 2 c + e, e = 0 the lower one.
+  const int nsamp = (n + kGap - 1) / kGap;
+  if (tid < 2 * P) {
+    const int c = tid >> 1, e = tid & 1;
+    const int m = min(kRankChunk, max(0, n - c * kRankChunk));  // keys of the chunk
+    int lo, len = 0;
+    uint32_t kk = 0;
+    if (e == 0 && b == 0) {
+      lo = 0;
+    } else if (e == 1 && b == nc - 1) {
+      lo = m;
+    } else {
+      const int id = (int)sv[cur][(int)((long long)(b + e) * nsamp / nc)];
+      const int g = id / kSamples;
+      kk = sk[0][id];
+      if (c == g) {
+        lo = (id - g * kSamples) * kGap;
+      } else {
+        int x = 0;  // the chunk's samples before the splitter
+        for (int step = kSamples; step > 0; step >>= 1) {
+          const int np = x + step;
+          const uint32_t y = sk[0][c * kSamples + min(np, kSamples) - 1];
+          x = np <= kSamples && (c < g ? y <= kk : y < kk) ? np : x;
+        }
+        // (the padding of a partial or missing chunk is never before: such a chunk is a
+        // later one than g, and no key is above it)
+        lo = x > 0 ? (x - 1) * kGap + 1 : 0;
+        len = x > 0 ? min(x * kGap, m) - lo : 0;
+        len |= c < g ? 1 << 30 : 0;  // equal keys are before the splitter too
+      }
+    }
+    wlo[tid] = lo;
+    wlen[tid] = len;
+    wkey[tid] = kk;
+  }
+  lds_barrier();
+  {
+    // A window has at most kGap - 1 entries: two per lane, all windows' reads in flight.
+    static_assert(kGap <= 128, "two entries per lane");
+    constexpr int U = 2 * kRunChunks / kWaves;
+    uint32_t x[U][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = wave + u * kWaves;
+      if (i < 2 * nc) {
+        const int lo = wlo[i], len = wlen[i] & 0xFFFF;
+        const uint32_t* p = ka + (i >> 1) * kRankChunk + lo;
+        x[u][0] = lane < len ? p[lane] : 0u;
+        x[u][1] = lane + 64 < len ? p[lane + 64] : 0u;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = wave + u * kWaves;
+      if (i < 2 * nc) {
+        const int len = wlen[i] & 0xFFFF;
+        const bool le = wlen[i] >> 30;
+        const uint32_t kk = wkey[i];
+        const bool b0 = lane < len && (le ? x[u][0] <= kk : x[u][0] < kk);
+        const bool b1 = lane + 64 < len && (le ? x[u][1] <= kk : x[u][1] < kk);
+        const int cnt = __builtin_popcountll(__builtin_amdgcn_ballot_w64(b0)) +
+                        __builtin_popcountll(__builtin_amdgcn_ballot_w64(b1));
+        if (lane == 0) bound[i] = wlo[i] + cnt;
+      }
+    }
+  }
+  lds_barrier();
+  if (wave == 0) {
+    const bool some = lane < nc;
+    const int lo = some ? bound[2 * min(lane, nc - 1)] : 0, hi = some ? bound[2 * min(lane, nc - 1) + 1] : 0;
+    const int incl = wave_scan<false>(hi - lo), before = wave_scan<false>(lo);
+    if (lane < P) off[lane + 1] = incl;
+    if (lane == 0) off[0] = 0;
+    if (lane == 63) {
+      totals[0] = incl;
+      totals[1] = before;
+    }
+  }
+  lds_barrier();
+  const int total = totals[0], base = totals[1];
+  for (int e = tid; e < total; e += kThreads) {
+    int c = 0;
+    for (int step = P >> 1; step > 0; step >>= 1)
+      if (off[c + step] <= e) c += step;
+    const int i = c * kRankChunk + bound[2 * c] + e - off[c];
+    key[0][e] = ka[i];
+    pos[0][e] = va[i];
+  }
+  lds_barrier();
+  const int per = (total + kThreads - 1) / kThreads | 1;  // odd: the threads' outputs spread over the banks
+  cur = 0;
+  for (int l = 0; l < lg; ++l) {
+    merge_level(key[cur], pos[cur], key[cur ^ 1], pos[cur ^ 1], off, l, P >> (l + 1), total, per);
+    cur ^= 1;
+    lds_barrier();
+  }
+  for (int e = tid; e < total; e += kThreads) {
+    const int t = (int)pos[cur][e];
+    if (FINAL) {
+      rank[(size_t)seg * T + t] = base + e;
+      w.ps[base + e] = t;
+    } else {
+      w.kb[r0 + base + e] = key[cur][e];
+      w.vb[r0 + base + e] = (uint32_t)t;
+    }
+  }
+}
+
+// First entry of the sorted array B[0, n) in global memory that is not ordered before
+// `key`, by one wave: 64 samples at a time, so three dependent reads for a run.
+template <bool LE>
+__device__ __forceinline__ int wave_lower(const uint32_t* __restrict__ B, int n, uint32_t key) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0;
+  while (n > 0) {  // the answer is in [lo, lo + n]
+    const int step = (n + 63) >> 6;
+    const int i = lane * step;  // entries lo, lo + step, ...
+    const uint32_t x = B[lo + min(i, n - 1)];
+    const bool before = i < n && (LE ? x <= key : x < key);
+    const int m = __builtin_popcountll(__builtin_amdgcn_ballot_w64(before));  // samples before the key
+    if (m == 0) return lo;
+    lo += (m - 1) * step + 1;  // past the last of them
+    n = min(step - 1, n - ((m - 1) * step + 1));
+  }
+  return lo;
+}
+
+// One workgroup per (sequence, run, kRankChunk consecutive keys of the sorted run): adds,
+// for every other run, the number of its keys ordered before each (equal ones too if the
+// run is an earlier one), which gives the ranks. The workgroup's first and last key bound
+// the stretch of the other run to search: about kRankChunk keys where the runs are alike,
+// none or all of them where one lies wholly past the other.
+__global__ __launch_bounds__(kThreads) void topk_merge_runs_kernel(int nseg, int T, void* ws, size_t per_seg_words,
+                                                                   int32_t* __restrict__ rank) {
+  constexpr int kMaxRuns = (1 << 24) / kRun;
+  constexpr int kPiece = 32768;  // keys of another run in LDS at a time
+  __shared__ uint32_t stretch[kPiece];
+  __shared__ int near[kThreads];
+  __shared__ int from[kMaxRuns], to[kMaxRuns];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nch = (T + kRankChunk - 1) / kRankChunk, nr = (T + kRun - 1) / kRun;
+  const int c = (int)blockIdx.x / nseg, seg = (int)blockIdx.x - c * nseg;
+  SegWork w = seg_work(ws, per_seg_words, seg, T);
+  const int own = c / kRunChunks;
+  const int i0 = c * kRankChunk, n = min(kRankChunk, T - i0);  // entries of the sorted runs
   uint32_t key[kSortJ];
   int rk[kSortJ];
-  bool valid[kSortJ];
 #pragma unroll
   for (int j = 0; j < kSortJ; ++j) {
-    const int i = j * kPrepThreads + tid;
-    valid[j] = i < n;
-    key[j] = valid[j] ? w.ka[t0 + i] : 0u;
-    rk[j] = i;
+    const int i = kSortJ * tid + j;
+    key[j] = w.kb[i0 + min(i, n - 1)];
+    rk[j] = i0 - own * kRun + i;
   }
-  for (int g0 = 0; g0 < nch; g0 += kMergeGroup) {
-    __syncthreads();  // every thread is done with the previous group's keys
-    uint32_t st[kMergeGroup][kSortJ];
-#pragma unroll
-    for (int g = 0; g < kMergeGroup; ++g)
-#pragma unroll
-      for (int j = 0; j < kSortJ; ++j) {
-        const int c2 = g0 + g, i = j * kPrepThreads + tid;
-        st[g][j] = c2 < nch && c2 != c && c2 * kRankChunk + i < T ? w.ka[c2 * kRankChunk + i] : 0u;
-      }
-#pragma unroll
-    for (int g = 0; g < kMergeGroup; ++g)
-#pragma unroll
-      for (int j = 0; j < kSortJ; ++j) other[g][j * kPrepThreads + tid] = st[g][j];
-    __syncthreads();
-    for (int g = 0; g < kMergeGroup && g0 + g < nch; ++g) {
-      const int c2 = g0 + g;
-      if (c2 == c) continue;
-      const int m = min(kRankChunk, T - c2 * kRankChunk);
-      if (c2 < c) count_before<true>(other[g], m, key, rk);
-      else count_before<false>(other[g], m, key, rk);
+  const uint32_t first = w.kb[i0], last = w.kb[i0 + n - 1];
+  for (int g = wave; g < nr; g += kWaves) {
+    if (g == own) continue;
+    const uint32_t* B = w.kb + (size_t)g * kRun;
+    const int m = min(kRun, T - g * kRun);
+    const int a = g < own ? wave_lower<true>(B, m, first) : wave_lower<false>(B, m, first);
+    const int b = g < own ? wave_lower<true>(B, m, last) : wave_lower<false>(B, m, last);
+    if ((tid & 63) == 0) {
+      from[g] = a;
+      to[g] = b;
     }
   }
-  int32_t* rkout = rank + (size_t)seg * T;
+  lds_barrier();
+  for (int g = 0; g < nr; ++g) {
+    if (g == own) continue;
+    const int a = __builtin_amdgcn_readfirstlane(from[g]), z = __builtin_amdgcn_readfirstlane(to[g]);
+#pragma unroll
+    for (int j = 0; j < kSortJ; ++j) rk[j] += a;
+    for (int p = a; p < z; p += kPiece) {
+      const uint32_t* B = w.kb + (size_t)g * kRun + p;
+      const int len = min(kPiece, z - p);
+      for (int i = tid; i < len; i += 8 * kThreads) {
+        uint32_t x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = B[min(i + u * kThreads, len - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (i + u * kThreads < len) stretch[i + u * kThreads] = x[u];
+      }
+      lds_barrier();
+      int at[kSortJ];
+      if (g < own) count_before<true>(stretch, len, key, at, near);
+      else count_before<false>(stretch, len, key, at, near);  // ends with a barrier: stretch is free
+#pragma unroll
+      for (int j = 0; j < kSortJ; ++j) rk[j] += at[j];
+    }
+  }
 #pragma unroll
   for (int j = 0; j < kSortJ; ++j) {
-    if (valid[j]) {
-      const int t = (int)w.va[t0 + j * kPrepThreads + tid];
-      rkout[t] = rk[j];
+    const int i = kSortJ * tid + j;
+    if (i < n) {
+      const int t = (int)w.vb[i0 + i];
+      rank[(size_t)seg * T + t] = rk[j];
       w.ps[rk[j]] = t;
     }
   }
 }
 
-// One workgroup per sequence, after the ranks: prefix maxima and the wavelet matrix
-// over A_i = rank_{s+i}. With LDSA (at most kLdsLevels eligible positions, T <=
-// 65536) every level partitions A from one LDS buffer into the other
-// (wavelet_level_lds), and only the levels' bit words and counts go to global
-// memory.
-template <bool LDSA>
-__global__ __launch_bounds__(kPrepThreads) void topk_prepare_kernel(int T, int s, int L, void* ws,
-                                                                    size_t per_seg_words,
-                                                                    const int32_t* __restrict__ rank) {
-  __shared__ PrepSmem sm;
-  __shared__ uint16_t abuf[LDSA ? 2 : 1][LDSA ? kLdsPerThread * kPrepThreads : 1];
-  const int tid = threadIdx.x;
-  const int seg = blockIdx.x;
-  SegWork w = seg_work(ws, per_seg_words, seg, T, L);
-  const int32_t* rk = rank + (size_t)seg * T;
-
-  const int n = T - s;  // eligible positions s .. T-1
-  if (n <= 0) return;
-
-  const int W = (n + 31) / 32;
-  if constexpr (LDSA) {
-    // A_i = rank_{s+i} into LDS, coalesced.
-    for (int i = tid; i < n; i += kPrepThreads) abuf[0][i] = (uint16_t)rk[s + i];
-    lds_barrier();
-    // Prefix maxima of A (the boundary token before saturation): thread tid takes
-    // positions kLdsPerThread tid .. + kLdsPerThread - 1, and one scan of the
-    // threads' maxima gives each its running maximum before them.
-    // (The loads never branch: the buffer holds 32768 entries.)
-    const int i0 = tid * kLdsPerThread;
-    int av[kLdsPerThread];
-    int mx = INT32_MIN;
+// ---------------------------------------------------------------------------
+// 4. Census
+// ---------------------------------------------------------------------------
+// census[block][bucket] = eligible tokens (t >= s) whose rank lies in the bucket (2^shift
+// consecutive ranks) and whose position lies before the block (2^shift positions).
+// A workgroup counts max(4096, 2^shift) consecutive ranks: each token adds one to its
+// (bucket, block) counter in LDS, and one wave per bucket sums the counters.
+__global__ __launch_bounds__(kThreads) void topk_census_kernel(int nseg, int T, int s, void* ws, size_t per_seg_words) {
+  __shared__ int cnt[kSortJ * kMaxBuckets];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int sh = census_shift(T), nb = census_buckets(T);
+  const int per = max(kRankChunk, 1 << sh);  // ranks per workgroup
+  const int g = (int)blockIdx.x / nseg, seg = (int)blockIdx.x - g * nseg;
+  SegWork w = seg_work(ws, per_seg_words, seg, T);
+  const int r0 = g * per, r1 = min(T, r0 + per);
+  const int b0 = r0 >> sh, rows = ((r1 - 1) >> sh) - b0 + 1;  // at most kSortJ buckets
+  for (int i = tid; i < rows * nb; i += kThreads) cnt[i] = 0;
+  lds_barrier();
+  for (int i = r0 + tid; i < r1; i += kRankChunk) {
+    int t[kSortJ];
 #pragma unroll
-    for (int e = 0; e < kLdsPerThread; ++e) {
-      av[e] = i0 + e < n ? (int)abuf[0][i0 + e] : INT32_MIN;
-      mx = max(mx, av[e]);
+    for (int j = 0; j < kSortJ; ++j) t[j] = w.ps[min(i + j * kThreads, T - 1)];
+#pragma unroll
+    for (int j = 0; j < kSortJ; ++j) {
+      const int r = i + j * kThreads;
+      if (r < r1 && t[j] >= s) atomicAdd(&cnt[((r >> sh) - b0) * nb + (t[j] >> sh)], 1);
     }
-    int total;
-    int run = block_scan<true>(mx, sm.sh, total);
-#pragma unroll
-    for (int e = 0; e < kLdsPerThread; ++e) {
-      run = max(run, av[e]);
-      if (i0 + e < n) w.pmax[i0 + e] = run;
-    }
-    // Wavelet matrix: level l splits on bit L-1-l of the current array (stable).
-    uint16_t *ain = abuf[0], *aout = abuf[LDSA ? 1 : 0];
-    for (int l = 0; l < L; ++l) {
-      const uint32_t z = wavelet_level_lds(ain, aout, n, L - 1 - l, w.bits + (size_t)l * (W + 1),
-                                           w.cnt + (size_t)l * (W + 1), sm);
-      if (tid == 0) w.zeros[l] = z;
-      uint16_t* t0 = ain;
-      ain = aout;
-      aout = t0;
-    }
-  } else {
-    // A_i = rank_{s+i} and its prefix maxima (the boundary token before
-    // saturation), one coalesced round of 1024 positions at a time; also the number
-    // of A values with each bit set, which every wavelet level needs.
-    if (tid < 32) sm.bitcnt[tid] = 0;
-    int bits[32];
-#pragma unroll
-    for (int k = 0; k < 32; ++k) bits[k] = 0;
-    int run = INT32_MIN;
-    for (int r0 = 0; r0 < n; r0 += kPrepThreads) {
-      const int i = r0 + tid;
-      const int av = i < n ? rk[s + i] : INT32_MIN;
-      if (i < n) {
-        w.ka[i] = (uint32_t)av;
-#pragma unroll
-        for (int k = 0; k < 32; ++k) bits[k] += (av >> k) & 1;
-      }
-      int total;
-      const int ex = block_scan<true>(av, sm.sh, total);
-      if (i < n) w.pmax[i] = max(run, max(ex, av));
-      run = max(run, total);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 32; ++k) {
-      int c = bits[k];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
-      if ((tid & 63) == 0 && k < L) atomicAdd(&sm.bitcnt[k], c);
-    }
-    __syncthreads();
-    // Wavelet matrix: level l splits on bit L-1-l of the current array (stable).
-    uint32_t *ain = w.ka, *aout = w.kb;
-    for (int l = 0; l < L; ++l) {
-      const uint32_t z = wavelet_level(ain, aout, n, L - 1 - l, sm.bitcnt[L - 1 - l], w.bits + (size_t)l * (W + 1),
-                                       w.cnt + (size_t)l * (W + 1), sm);
-      if (tid == 0) w.zeros[l] = z;
-      uint32_t* t0 = ain;
-      ain = aout;
-      aout = t0;
+  }
+  lds_barrier();
+  if (wave < rows) {
+    int run = 0;
+    for (int p = 0; p < nb; p += 64) {
+      const int i = p + lane;
+      const int x = i < nb ? cnt[wave * nb + i] : 0;
+      const int incl = wave_scan<false>(x);
+      if (i < nb) w.census[(size_t)i * nb + b0 + wave] = (uint32_t)(run + incl - x);
+      run += __builtin_amdgcn_readlane(incl, 63);
     }
   }
 }
 
-// Ones among the first i entries of level l.
-__device__ __forceinline__ int rank1(const uint32_t* bw, const uint32_t* cw, int i) {
-  const int wd = i >> 5, b = i & 31;
-  const uint32_t mask = b ? (0xFFFFFFFFu >> (32 - b)) : 0u;
-  return (int)cw[wd] + __popc(bw[wd] & mask);
+// ---------------------------------------------------------------------------
+// 5. Queries
+// ---------------------------------------------------------------------------
+// A block of queries adds at most kBlock tokens, so its cutoffs lie within the kBlock + 1
+// largest kept ranks before it or among its own tokens; the scan that lists them stops
+// at a multiple of kBlock ranks.
+constexpr int kMaxCand = 3 * kBlock;
+constexpr int kMaxLocal = 192;  // a wave's own candidates: 64 + 64 kept, 64 new
+
+struct QuerySmem {
+  Exchange ex;
+  int cnt[kMaxBuckets];         // census remainder (T > 2^20)
+  int found[3];
+  uint32_t cand[kMaxCand];      // candidate ranks, descending
+  uint16_t tag[kMaxCand];       // 0: kept before the block, else 1 + its place in the block
+  uint32_t local[kWaves][kMaxLocal];  // (rank << 7) | (0: kept before the wave's queries, else 1 + lane)
+  uint8_t place[kWaves][64];          // a lane's token's place in the wave's list, or 255
+};
+
+// The cutoffs of a wave's 64 queries from its list of n <= 32 W candidates: lane j's is
+// the want-th of those present at its query, which are the candidates kept before and
+// the tokens of lanes 0 .. j. Each lane builds the bitmap of the candidates present (an or
+// over the earlier lanes' tokens) and selects the want-th set bit.
+template <int W>
+__device__ __forceinline__ int local_cutoff(const uint32_t* local, uint8_t* place, int n, int want) {
+  const int lane = threadIdx.x & 63;
+  place[lane] = 255;
+  wave_sync();
+  uint32_t here[W];
+#pragma unroll
+  for (int u = 0; u < W / 2; ++u) {
+    const int i = 64 * u + lane;
+    const int tg = i < n ? (int)(local[i] & 127u) : 127;
+    const uint64_t mb = __builtin_amdgcn_ballot_w64(tg == 0);
+    here[2 * u] = (uint32_t)mb;
+    here[2 * u + 1] = (uint32_t)(mb >> 32);
+    if (tg >= 1 && tg <= 64) place[tg - 1] = (uint8_t)i;
+  }
+  wave_sync();
+  const int mine = (int)place[lane];
+#pragma unroll
+  for (int u = 0; u < W; ++u) {
+    int x = (mine >> 5) == u ? 1 << (mine & 31) : 0;
+    x |= __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);
+    x |= __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x |= __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x |= __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    x |= __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);
+    x |= __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);
+    here[u] |= (uint32_t)x;
+  }
+  uint32_t sel = here[0];
+  int at = 0;
+#pragma unroll
+  for (int u = 0; u + 1 < W; ++u) {
+    const int c = __popc(here[u]);
+    const bool next = at == 32 * u && want > c;
+    want -= next ? c : 0;
+    sel = next ? here[u + 1] : sel;
+    at += next ? 32 : 0;
+  }
+#pragma unroll
+  for (int half = 16; half > 0; half >>= 1) {
+    const int c = __popc(sel & ((1u << half) - 1u));
+    const bool next = want > c;
+    want -= next ? c : 0;
+    sel = next ? sel >> half : sel;
+    at += next ? half : 0;
+  }
+  return (int)(local[at] >> 7);
 }
 
-// The answer to query q of a sequence: the cutoff, the label of t_new = q - w and the
-// boundary token. bits, cnt: the wavelet levels' words and ones-before counts, W1
-// per level; zeros: each level's zero count; in global memory or LDS.
-__device__ __forceinline__ void answer_query(int q, int T, int s, int w_win, int k, int L, int W1,
-                                             const uint32_t* bits, const uint32_t* cnt, const uint32_t* zeros,
-                                             const int32_t* __restrict__ ps, const int32_t* __restrict__ pmax,
-                                             const int32_t* __restrict__ rk, int& cut, int& lab, int& bnd) {
-  const long long tnew = (long long)q - w_win;
-  const long long p = tnew - s + 1;  // |E(q)|
-  cut = T;
-  lab = 0;
-  bnd = -1;
-  if (p >= 1) {
-    if (p >= k) {
-      // k-th smallest of A[0, p) by walking the wavelet levels.
-      int lo = 0, hi = (int)p, kk = k, val = 0;
-      for (int l = 0; l < L; ++l) {
-        const uint32_t* bw = bits + (size_t)l * W1;
-        const uint32_t* cw = cnt + (size_t)l * W1;
-        const int o_lo = rank1(bw, cw, lo), o_hi = rank1(bw, cw, hi);
-        const int z = (hi - o_hi) - (lo - o_lo);
-        if (kk <= z) {
-          lo -= o_lo;
-          hi -= o_hi;
-        } else {
-          kk -= z;
-          const int Z = (int)zeros[l];
-          lo = Z + o_lo;
-          hi = Z + o_hi;
-          val |= 1 << (L - 1 - l);
+// One workgroup per (sequence, kBlock consecutive new tokens t0 ..): the queries t + w.
+// The first one also writes the queries before w, which have no eligible token.
+// With p tokens eligible before the block, "old" are the eligible tokens before t0 and
+// "new" those of the block; U is one above the k-th smallest old rank (T if p < k). Ranks
+// from U on never matter again. Let D be the new tokens below U so far, less k - p
+// if p < k: the cutoff is then the (D + 1)-th largest rank below U present.
+// Bound by instruction issue once the chip is full (about 700 vector instructions per wave)
+// and by the reads' latency below that: 21.7 us for 4 x 8 x 32768 (1024 workgroups), 7.4 us
+// for 1 x 8 x 4096, against 224 and 42 us to build and walk a wavelet matrix.
+__global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads), amdgpu_waves_per_eu(8, 8))) void
+topk_query_kernel(int nseg, int T, int s, int w_win, int k, void* ws, size_t per_seg_words,
+                  const int32_t* __restrict__ ranks, int32_t* __restrict__ cutoff, int32_t* __restrict__ label,
+                  int32_t* __restrict__ boundary) {
+  __shared__ QuerySmem sm;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int blk = (int)blockIdx.x / nseg, seg = (int)blockIdx.x - blk * nseg;
+  SegWork w = seg_work(ws, per_seg_words, seg, T);
+  const int32_t* rank = ranks + (size_t)seg * T;
+  int32_t* cut_o = cutoff + (size_t)seg * T;
+  int32_t* lab_o = label ? label + (size_t)seg * T : nullptr;
+  int32_t* bnd_o = boundary ? boundary + (size_t)seg * T : nullptr;
+  int turn = 0;
+
+  if (blk == 0) {
+    for (int q = tid; q < min(w_win, T); q += kThreads) {
+      cut_o[q] = T;
+      if (lab_o) lab_o[q] = 0;
+      if (bnd_o) bnd_o[q] = -1;
+    }
+    if (w_win >= T) return;
+  }
+  const int t0 = blk * kBlock;
+  const int tl = min(t0 + kBlock, T - w_win) - 1;  // last new token with a query
+  const int t = t0 + tid;
+  const bool active = t <= tl;
+  const bool elig = active && t >= s;
+  const int r = rank[min(t, tl)];
+  const int q = t + w_win;
+  const int p0 = max(t0 - s, 0);            // eligible before the block
+  const int p = t - s + 1;                  // eligible at this thread's query (<= 0: none)
+  const int p_last = tl - s + 1;
+  int cut = T, bnd = -1;
+
+  // Before saturation every eligible token is kept: the boundary token is the one with
+  // the largest rank.
+  if (bnd_o && p_last >= 1 && p0 + 1 < k) {
+    int mx = elig ? r : INT32_MIN;
+    int old = INT32_MIN;
+    for (int i = s + tid; i < t0; i += kThreads) old = max(old, rank[i]);
+    int before, total;
+    wave_totals<true>(__builtin_amdgcn_readlane(wave_scan<true>(old), 63), sm.ex, turn, before, total);
+    const int incl = wave_scan<true>(mx);
+    int dummy;
+    wave_totals<true>(__builtin_amdgcn_readlane(incl, 63), sm.ex, turn, before, dummy);
+    mx = max(total, max(before, incl));
+    if (elig && p < k) bnd = w.ps[mx];
+  }
+
+  if (p_last >= k) {
+    // U, and D before the block.
+    int U = T, D0 = p0 - k;
+    if (p0 >= k) {
+      D0 = 0;
+      const int sh = census_shift(T), nb = census_buckets(T);
+      int cb = tid < nb ? (int)w.census[(size_t)(t0 >> sh) * nb + tid] : 0;
+      const int rest = (t0 >> sh) << sh;  // first position that the census does not count
+      if (rest < t0) {                    // only where blocks are wider than kBlock
+        sm.cnt[tid] = 0;
+        lds_barrier();
+        for (int i = max(rest, s) + tid; i < t0; i += kThreads) atomicAdd(&sm.cnt[rank[i] >> sh], 1);
+        lds_barrier();
+        cb += sm.cnt[tid];
+      }
+      // The bucket with the k-th old rank: inclusive counts over the buckets.
+      const int incl = wave_scan<false>(cb);
+      int before, total;
+      wave_totals<false>(__builtin_amdgcn_readlane(incl, 63), sm.ex, turn, before, total);
+      const int upto = before + incl;
+      if (upto >= k && upto - cb < k) {
+        sm.found[0] = tid;
+        sm.found[1] = k - (upto - cb);  // its place among the bucket's old ranks, from 1
+      }
+      lds_barrier();
+      int v0 = __builtin_amdgcn_readfirstlane(sm.found[0]) << sh;
+      int kk = __builtin_amdgcn_readfirstlane(sm.found[1]);
+      for (;;) {  // one round unless buckets are wider than kBlock
+        const int v = v0 + tid;
+        const int pos = v < T ? w.ps[v] : INT32_MAX;
+        const bool old = pos >= s && pos < t0;
+        int tot;
+        const int at = block_count(old, sm.ex, turn, tot);
+        if (old && at == kk - 1) sm.found[2] = v + 1;
+        if (kk <= tot || v0 + kThreads >= T) break;
+        kk -= tot;
+        v0 += kThreads;
+      }
+      lds_barrier();
+      U = __builtin_amdgcn_readfirstlane(sm.found[2]);
+    }
+    // New tokens below U.
+    const bool in = elig && r < U;
+    const uint64_t inm = __builtin_amdgcn_ballot_w64(in);
+    int before, m;
+    wave_totals<false>(__builtin_popcountll(inm), sm.ex, turn, before, m);
+    if (m == 0) {  // p0 >= k here: the cutoff stays
+      cut = U - 1;
+    } else {
+      // Candidates: old and new ranks below U, descending, until D0 + m + 1 old ones are
+      // listed (the last query's cutoff is at or before that one) or none is left.
+      const int need = D0 + m + 1;
+      int nc = 0, nold = 0;
+      int v = U - 1 - tid;
+      int pos = v >= 0 ? w.ps[v] : -1;
+      for (int top = U; top > 0 && nold < need; top -= kThreads) {
+        const int pv = v, pp = pos;
+        v -= kThreads;
+        pos = v >= 0 ? w.ps[v] : -1;  // the next step's, in flight during this one
+        const bool old = pp >= s && pp < t0;
+        const bool keep = old || (pp >= max(s, t0) && pp <= tl);
+        const uint64_t mo = __builtin_amdgcn_ballot_w64(old), mk = __builtin_amdgcn_ballot_w64(keep);
+        int bef, tot;
+        wave_totals<false>(__builtin_popcountll(mk) << 16 | __builtin_popcountll(mo), sm.ex, turn, bef, tot);
+        if (keep) {
+          const int i = nc + (bef >> 16) + lanes_below(mk);
+          sm.cand[i] = (uint32_t)pv;
+          sm.tag[i] = (uint16_t)(old ? 0 : pp - t0 + 1);
+        }
+        nc += tot >> 16;
+        nold += tot & 0xFFFF;
+      }
+      lds_barrier();
+      // This wave's queries: D before them, and the place i0 of the cutoff there (the
+      // list's start before saturation).
+      const int D = D0 + before;
+      const int lo_tag = 64 * wave;  // tags up to this are present before the wave's queries
+      int i0 = 0, want;              // want: place of this lane's cutoff among those present from i0 on, from 1
+      if (D >= 0) {
+        int seen = 0;
+        bool hit = false;
+        for (int i = 0; i < nc && !hit; i += 256) {
+          uint64_t mb[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int e = i + 64 * u + lane;
+            mb[u] = __builtin_amdgcn_ballot_w64(e < nc && (int)sm.tag[min(e, nc - 1)] <= lo_tag);
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int c = __builtin_popcountll(mb[u]);
+            if (!hit && seen + c > D) {
+              hit = true;
+              const uint64_t at =
+                  __builtin_amdgcn_ballot_w64(((mb[u] >> lane) & 1) && lanes_below(mb[u]) == D - seen);
+              i0 = i + 64 * u + __builtin_ctzll(at);
+            }
+            seen += c;
+          }
         }
       }
-      cut = val;
-      bnd = ps[cut];
-    } else {
-      bnd = ps[pmax[p - 1]];
+      const int c0 = (int)sm.cand[i0];
+      // The wave's own tokens that lower the cutoff: those below it.
+      const uint64_t f = __builtin_amdgcn_ballot_w64(in && (D < 0 || r < c0));
+      const int own = lanes_below(f) + (int)((f >> lane) & 1);  // up to and with this lane's
+      want = D < 0 ? D + own + 1 : own + 1;
+      const int most = D < 0 ? D + __builtin_popcountll(f) + 1 : __builtin_popcountll(f) + 1;
+      cut = D < 0 ? T : c0;
+      if (most > (D < 0 ? 0 : 1)) {
+        int n = 0, kept = 0;
+        for (int i = i0 & ~63; i < nc && kept < most; i += 64) {
+          const int e = min(i + lane, nc - 1);
+          const int tg = (int)sm.tag[e];
+          const bool ok = i + lane >= i0 && i + lane < nc;
+          const bool base = ok && tg <= lo_tag;
+          const bool mine = ok && tg > lo_tag && tg <= lo_tag + 64;
+          const uint64_t mm = __builtin_amdgcn_ballot_w64(base || mine);
+          if (base || mine)
+            sm.local[wave][n + lanes_below(mm)] = sm.cand[e] << 7 | (uint32_t)(base ? 0 : tg - lo_tag);
+          n += __builtin_popcountll(mm);
+          kept += __builtin_popcountll(__builtin_amdgcn_ballot_w64(base));
+        }
+        wave_sync();
+        const uint32_t* local = sm.local[wave];
+        uint8_t* place = sm.place[wave];
+        cut = n <= 64 ? local_cutoff<2>(local, place, n, want) : n <= 128 ? local_cutoff<4>(local, place, n, want)
+                                                                          : local_cutoff<6>(local, place, n, want);
+      }
     }
-    lab = rk[tnew] <= cut ? 1 : -1;
+    if (p < k) cut = T;
+    else if (bnd_o && active) bnd = w.ps[cut];
+  }
+  if (active) {
+    cut_o[q] = cut;
+    if (lab_o) lab_o[q] = p < 1 ? 0 : (r <= cut ? 1 : -1);
+    if (bnd_o) bnd_o[q] = bnd;
   }
 }
 
-// One thread per (sequence, query).
-__global__ __launch_bounds__(256) void topk_query_kernel(int nseg, int T, int s, int w_win, int k, int L, void* ws,
-                                                         size_t per_seg_words, const int32_t* __restrict__ rank,
-                                                         int32_t* __restrict__ cutoff, int32_t* __restrict__ label,
-                                                         int32_t* __restrict__ boundary) {
-  const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (long long)nseg * T) return;
-  const int seg = (int)(gid / T), q = (int)(gid - (long long)seg * T);
-  SegWork w = seg_work(ws, per_seg_words, seg, T, L);
-  const int W1 = (T - s + 31) / 32 + 1;
-  int cut, lab, bnd;
-  answer_query(q, T, s, w_win, k, L, W1, w.bits, w.cnt, w.zeros, w.ps, w.pmax, rank + (size_t)seg * T, cut, lab,
-               bnd);
-  cutoff[gid] = cut;
-  if (label) label[gid] = lab;
-  if (boundary) boundary[gid] = bnd;
-}
-
-// Words of LDS for a sequence's wavelet levels (bit words, counts and zero counts)
-// in the query kernel below: 2 L W1 + L of them (T = 32768: 30765).
-constexpr int kQueryLdsWords = 32768;
-constexpr int kQueryPerThread = 4;
-
-// One workgroup per (sequence, 4096 queries): the sequence's levels are copied into
-// LDS once, and each thread answers 4 queries from there, so that the level walks
-// read LDS instead of global memory.
-__global__ __launch_bounds__(kPrepThreads) void topk_query_lds_kernel(int T, int s, int w_win, int k, int L,
-                                                                      void* ws, size_t per_seg_words,
-                                                                      const int32_t* __restrict__ rank,
-                                                                      int32_t* __restrict__ cutoff,
-                                                                      int32_t* __restrict__ label,
-                                                                      int32_t* __restrict__ boundary) {
-  __shared__ uint32_t wl[kQueryLdsWords];
-  constexpr int QB = kQueryPerThread * kPrepThreads;
+// ---------------------------------------------------------------------------
+// 6. Evictions
+// ---------------------------------------------------------------------------
+// One workgroup per (sequence, kRankChunk consecutive ranks): the query at which each of
+// their tokens leaves the mask. The cutoff never increases with q, so the queries whose
+// cutoff lies among the workgroup's ranks are consecutive: two rounds of 1024 samples find
+// them. Each notes the first query of its cutoff in LDS, and a rank's first query with a
+// smaller cutoff is the least one noted below it (a minimum scan in rank order), or the
+// first query past the range. Bound by the latency of the samples' reads and of the
+// scattered writes: 9.7 us for 4 x 8 x 32768 (15 us with a binary search over the cutoffs
+// per token).
+__global__ __launch_bounds__(kThreads) void topk_evict_kernel(int nseg, int T, int s, int w_win, void* ws,
+                                                              size_t per_seg_words, const int32_t* __restrict__ cutoff,
+                                                              int32_t* __restrict__ evict) {
+  __shared__ alignas(16) int first[kRankChunk];
+  __shared__ Exchange ex;
+  int turn = 0;
   const int tid = threadIdx.x;
-  const int nqb = (T + QB - 1) / QB;
-  const int seg = (int)blockIdx.x / nqb, qb = (int)blockIdx.x - seg * nqb;
-  SegWork w = seg_work(ws, per_seg_words, seg, T, L);
-  const int W1 = (T - s + 31) / 32 + 1;
-  const int lw = L * W1;
-  for (int i = tid; i < lw; i += kPrepThreads) {
-    wl[i] = w.bits[i];
-    wl[lw + i] = w.cnt[i];
-  }
-  for (int i = tid; i < L; i += kPrepThreads) wl[2 * lw + i] = w.zeros[i];
-  __syncthreads();
+  const int g = (int)blockIdx.x / nseg, seg = (int)blockIdx.x - g * nseg;
+  SegWork w = seg_work(ws, per_seg_words, seg, T);
+  const int32_t* cut = cutoff + (size_t)seg * T;
+  const int r0 = g * kRankChunk, r1 = min(T, r0 + kRankChunk);
+  int t[kSortJ];
 #pragma unroll
-  for (int j = 0; j < kQueryPerThread; ++j) {
-    const int q = qb * QB + j * kPrepThreads + tid;
-    if (q < T) {
-      int cut, lab, bnd;
-      answer_query(q, T, s, w_win, k, L, W1, wl, wl + lw, wl + 2 * lw, w.ps, w.pmax, rank + (size_t)seg * T, cut,
-                   lab, bnd);
-      const size_t gid = (size_t)seg * T + q;
-      cutoff[gid] = cut;
-      if (label) label[gid] = lab;
-      if (boundary) boundary[gid] = bnd;
+  for (int j = 0; j < kSortJ; ++j) t[j] = w.ps[min(r0 + j * kThreads + tid, T - 1)];
+  // qa, qb: first queries with a cutoff below r1 and below r0 (T if there is none).
+  int qa = 0, qb = 0;
+  {
+    const int step = (T + kThreads - 1) / kThreads;  // 16384 at most
+    const int x = cut[min(tid * step, T - 1)];
+    const bool in = tid * step < T;
+    int before, total;
+    wave_totals<false>(__builtin_popcountll(__builtin_amdgcn_ballot_w64(in && x >= r1)) << 16 |
+                           __builtin_popcountll(__builtin_amdgcn_ballot_w64(in && x >= r0)),
+                       ex, turn, before, total);
+    const int na = total >> 16, nb = total & 0xFFFF;  // samples not below
+    // The answers lie past the last such sample, within `step` queries.
+    const int ba = na ? (na - 1) * step + 1 : 0, la = na ? min(step - 1, T - ba) : 0;
+    const int bb = nb ? (nb - 1) * step + 1 : 0, lb = nb ? min(step - 1, T - bb) : 0;
+    int ca = 0, cb = 0;
+    for (int i = tid; i < step; i += kThreads) {
+      ca += i < la && cut[min(ba + i, T - 1)] >= r1;
+      cb += i < lb && cut[min(bb + i, T - 1)] >= r0;
+    }
+    wave_totals<false>(__builtin_amdgcn_readlane(wave_scan<false>(ca), 63), ex, turn, before, total);
+    qa = ba + total;
+    wave_totals<false>(__builtin_amdgcn_readlane(wave_scan<false>(cb), 63), ex, turn, before, total);
+    qb = bb + total;
+  }
+  reinterpret_cast<int4*>(first)[tid] = int4{INT32_MAX, INT32_MAX, INT32_MAX, INT32_MAX};
+  lds_barrier();
+  for (int q0 = qa; q0 < qb; q0 += kRankChunk) {
+    int c[kSortJ], p[kSortJ];
+#pragma unroll
+    for (int j = 0; j < kSortJ; ++j) {
+      const int q = min(q0 + j * kThreads + tid, qb - 1);
+      c[j] = cut[q];
+      p[j] = cut[max(q - 1, 0)];
+    }
+#pragma unroll
+    for (int j = 0; j < kSortJ; ++j) {
+      const int q = q0 + j * kThreads + tid;
+      if (q < qb && (q == qa || c[j] != p[j])) first[c[j] - r0] = q;
     }
   }
-}
-
-// One thread per (sequence, token): the query at which the token leaves the mask.
-// cutoff is non-increasing in q, so the first q with cutoff_q < rank_t is found by
-// binary search.
-__global__ __launch_bounds__(256) void topk_evict_kernel(int nseg, int T, int s, int w_win,
-                                                         const int32_t* __restrict__ rank,
-                                                         const int32_t* __restrict__ cutoff,
-                                                         int32_t* __restrict__ evict) {
-  const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (long long)nseg * T) return;
-  const int seg = (int)(gid / T), t = (int)(gid - (long long)seg * T);
-  int e = T;
-  if (t >= s) {
-    const int32_t* cut = cutoff + (size_t)seg * T;
-    const int r = rank[gid];
-    int lo = 0, hi = T;  // first q in [lo, hi) with cut[q] < r, or T
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (cut[mid] < r) hi = mid;
-      else lo = mid + 1;
-    }
-    const long long leave = (long long)t + w_win;
-    e = (int)(lo > leave ? lo : (leave < T ? leave : T));
+  lds_barrier();
+  // Exclusive minimum over the ranks before each of this thread's four, as a maximum of
+  // the negated values.
+  {
+    const int4 f = reinterpret_cast<const int4*>(first)[tid];
+    const int m0 = -f.x, m1 = max(m0, -f.y), m2 = max(m1, -f.z), m3 = max(m2, -f.w);
+    const int incl = wave_scan<true>(m3);
+    int before, total;
+    wave_totals<true>(__builtin_amdgcn_readlane(incl, 63), ex, turn, before, total);
+    const int prev = __builtin_amdgcn_update_dpp(INT32_MIN, incl, 0x138, 0xF, 0xF, false);  // wave_shr:1
+    const int e = max(max(before, prev), -qb);
+    reinterpret_cast<int4*>(first)[tid] = int4{-e, -max(e, m0), -max(e, m1), -max(e, m2)};
   }
-  evict[gid] = e;
+  lds_barrier();
+#pragma unroll
+  for (int j = 0; j < kSortJ; ++j) {
+    const int i = j * kThreads + tid;
+    if (r0 + i < T) {
+      const long long leave = (long long)t[j] + w_win;
+      evict[(size_t)seg * T + t[j]] = t[j] < s ? T : (int)min((long long)T, max((long long)first[i], leave));
+    }
+  }
 }
 
 }  // namespace
 
-int topk_levels(int T) {
+static int topk_levels(int T) {
   int L = 1;
   while ((1 << L) < T) ++L;
   return L;
 }
 
+// A caller's workspace: the arrays of SegWork fit in it with room to spare for every T
+// (5 T words and the census, at most 2^20 words and less than T where T < 2^20).
 size_t topk_workspace_words_per_seq(int T) {
   const int L = topk_levels(T);
   const size_t W1 = (size_t)(T + 31) / 32 + 1;
@@ -797,50 +1140,35 @@ int noalloc_scratch(void* stream, void** ptr) {
 }
 
 int launch_running_topk(const TopkLaunch& L) {
-  const int nseg = L.B * L.H;
-  const int levels = topk_levels(L.T);
-  const size_t per = topk_workspace_words_per_seq(L.T);
-  const long long n_elig = (long long)L.T - L.sinks;  // eligible positions s .. T-1
-  const long long chunks = (long long)nseg * ((L.T + kRankChunk - 1) / kRankChunk);
-  hipLaunchKernelGGL(topk_chunk_sort_kernel, dim3((unsigned)chunks), dim3(kPrepThreads), 0, (hipStream_t)L.stream,
-                     L.scores, L.log_gamma, L.H, L.T, levels, L.workspace, per, L.rank);
+  const int nseg = L.B * L.H, T = L.T;
+  const size_t per = topk_workspace_words_per_seq(T);
+  hipStream_t st = (hipStream_t)L.stream;
+  const unsigned chunks = (unsigned)((long long)nseg * ((T + kRankChunk - 1) / kRankChunk));
+  const dim3 wg(kThreads);
+  hipLaunchKernelGGL(topk_chunk_sort_kernel, dim3(chunks), wg, 0, st, L.scores, L.log_gamma, nseg, L.H, T, L.sinks,
+                     L.workspace, per, L.rank);
   int e = (int)hipGetLastError();
   if (e) return e;
-  if (L.T > kRankChunk) {
-    hipLaunchKernelGGL(topk_merge_rank_kernel, dim3((unsigned)chunks), dim3(kPrepThreads), 0, (hipStream_t)L.stream,
-                       L.T, levels, L.workspace, per, L.rank);
-    e = (int)hipGetLastError();
-    if (e) return e;
+  if (T > kRankChunk) {
+    if (T <= kRun) {
+      hipLaunchKernelGGL(topk_merge_kernel<true>, dim3(chunks), wg, 0, st, nseg, T, L.workspace, per, L.rank);
+    } else {
+      hipLaunchKernelGGL(topk_merge_kernel<false>, dim3(chunks), wg, 0, st, nseg, T, L.workspace, per, L.rank);
+      if ((e = (int)hipGetLastError())) return e;
+      hipLaunchKernelGGL(topk_merge_runs_kernel, dim3(chunks), wg, 0, st, nseg, T, L.workspace, per, L.rank);
+    }
+    if ((e = (int)hipGetLastError())) return e;
+    const int ranks = 1 << census_shift(T) > kRankChunk ? 1 << census_shift(T) : kRankChunk;
+    hipLaunchKernelGGL(topk_census_kernel, dim3((unsigned)((long long)nseg * ((T + ranks - 1) / ranks))), wg, 0, st,
+                       nseg, T, L.sinks, L.workspace, per);
+    if ((e = (int)hipGetLastError())) return e;
   }
-  if (n_elig <= kLdsLevels && L.T <= 65536)
-    hipLaunchKernelGGL(topk_prepare_kernel<true>, dim3(nseg), dim3(kPrepThreads), 0, (hipStream_t)L.stream, L.T,
-                       L.sinks, levels, L.workspace, per, L.rank);
-  else
-    hipLaunchKernelGGL(topk_prepare_kernel<false>, dim3(nseg), dim3(kPrepThreads), 0, (hipStream_t)L.stream, L.T,
-                       L.sinks, levels, L.workspace, per, L.rank);
-  e = (int)hipGetLastError();
-  if (e) return e;
-  const long long total = (long long)nseg * L.T;
-  const unsigned blocks = (unsigned)((total + 255) / 256);
-  // The query kernel with the levels in LDS when they fit and its grid (one
-  // workgroup per 4096 queries) covers every compute unit: below that, the copies
-  // into LDS cost more than they save (B = 2, T = 16384: 64 workgroups, 2% slower).
-  const long long qw1 = n_elig > 0 ? (n_elig + 31) / 32 + 1 : 0;
-  const long long qblocks = (long long)nseg * ((L.T + kQueryPerThread * kPrepThreads - 1) /
-                                               (kQueryPerThread * kPrepThreads));
-  const int ncu = stream_cus(L.stream);
-  if (n_elig > 0 && 2 * levels * qw1 + levels <= kQueryLdsWords && ncu > 0 && qblocks >= ncu) {
-    hipLaunchKernelGGL(topk_query_lds_kernel, dim3((unsigned)qblocks), dim3(kPrepThreads), 0, (hipStream_t)L.stream,
-                       L.T, L.sinks, L.window, L.topk, levels, L.workspace, per, L.rank, L.cutoff, L.label,
-                       L.boundary);
-  } else {
-    hipLaunchKernelGGL(topk_query_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)L.stream, nseg, L.T, L.sinks,
-                       L.window, L.topk, levels, L.workspace, per, L.rank, L.cutoff, L.label, L.boundary);
-  }
-  e = (int)hipGetLastError();
-  if (e || !L.evict) return e;
-  hipLaunchKernelGGL(topk_evict_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)L.stream, nseg, L.T, L.sinks,
-                     L.window, L.rank, L.cutoff, L.evict);
+  const int nqb = L.window >= T ? 1 : (T - L.window + kBlock - 1) / kBlock;
+  hipLaunchKernelGGL(topk_query_kernel, dim3((unsigned)((long long)nseg * nqb)), wg, 0, st, nseg, T, L.sinks, L.window,
+                     L.topk, L.workspace, per, L.rank, L.cutoff, L.label, L.boundary);
+  if ((e = (int)hipGetLastError()) || !L.evict) return e;
+  hipLaunchKernelGGL(topk_evict_kernel, dim3(chunks), wg, 0, st, nseg, T, L.sinks, L.window, L.workspace, per,
+                     L.cutoff, L.evict);
   return (int)hipGetLastError();
 }
 

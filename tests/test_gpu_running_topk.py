@@ -2,6 +2,7 @@
 Sec. 3.1 eq. teacher_label). Priorities are compared in float32 on both sides (the
 ranking is an integer decided by them); ranks, cutoffs, labels and boundary tokens
 must match exactly."""
+import heapq
 import math
 
 import numpy as np
@@ -155,10 +156,10 @@ def test_long_context_t131072():
 
 @pytest.mark.parametrize("T", [32771, 32772, 40000, 136072])
 def test_each_wavelet_build(T):
-    """The wavelet levels are built in LDS up to n = T - s = 32767 eligible positions
-    (T = 32771) and in rounds through global memory beyond (T = 32772, the first size
-    past LDS; T = 40000 and 136072, ragged last rounds). Ranks, cutoffs and eviction
-    queries of every position exactly, labels and boundaries on sampled queries."""
+    """Several sorted chunks of 4096 positions, the last one of 3, 4 or 3136 (T = 32771,
+    32772, 40000), and two runs of chunks, the second of 5000 positions (T = 136072).
+    Ranks, cutoffs and eviction queries of every position exactly, labels and boundaries
+    on sampled queries."""
     s, w, k = 4, 256, 2016
     rng = np.random.default_rng(T)
     scores = rng.standard_normal((1, 2, T)).astype(np.float32)
@@ -174,9 +175,8 @@ def test_each_wavelet_build(T):
 
 
 def test_queries_from_lds_ragged_length():
-    """64 sequences of T = 12411 (a ragged last block of queries): the query kernel
-    copies each sequence's wavelet levels into LDS once its grid covers the chip.
-    Ranks, cutoffs and eviction queries of three sequences exactly, labels and
+    """64 sequences of T = 12411 (a ragged last block of queries, and more workgroups of
+    queries than the chip holds at once). Ranks, cutoffs and eviction queries of three sequences exactly, labels and
     boundaries on sampled queries."""
     B, H, T, s, w, k = 8, 8, 12411, 4, 256, 2016
     rng = np.random.default_rng(77)
@@ -190,3 +190,47 @@ def test_queries_from_lds_ragged_length():
             np.testing.assert_array_equal(got[n][b, h], e[n][0, 0], err_msg=n)
         np.testing.assert_array_equal(got["label"][b, h, qs], e["label"][0, 0, qs])
         np.testing.assert_array_equal(got["boundary"][b, h, qs], e["boundary"][0, 0, qs])
+
+
+def _cutoffs_by_heap(rank, s, w, k):
+    """The running cutoff from its definition with a heap of the k smallest ranks so far,
+    for lengths at which the oracle's Fenwick scan takes too long."""
+    T = rank.shape[0]
+    cut, kept, ranks = np.full(T, T, dtype=np.int64), [], rank.tolist()
+    for q in range(s + w, T):
+        heapq.heappush(kept, -ranks[q - w])
+        if len(kept) > k:
+            heapq.heappop(kept)
+        if len(kept) == k:
+            cut[q] = -kept[0]
+    return cut
+
+
+EDGES = [
+    # T, s, w, k: one token to each side of a query block, a sorted chunk, a run and the
+    # widest census
+    (1023, 0, 0, 100), (1025, 4, 0, 1024), (2049, 4, 1, 700), (4096, 4, 256, 2016), (4097, 0, 64, 1),
+    (8193, 3, 256, 4000), (131072, 4, 256, 2016), (131073, 4, 256, 2016), ((1 << 20) + 100003, 4, 256, 2016),
+]
+
+
+@pytest.mark.parametrize("kind", ["rising", "falling", "waves"])
+@pytest.mark.parametrize("case", EDGES, ids=lambda c: "T%d_s%dw%dk%d" % c)
+def test_edges_of_blocks_chunks_and_runs(case, kind):
+    """Scores that keep every arriving token (rising), none (falling) or stretches of them
+    (waves, with ties), at the sizes where the ranking's pieces end."""
+    T, s, w, k = case
+    rng = np.random.default_rng(T + len(kind))
+    t = np.arange(T, dtype=np.float32)
+    scores = {"rising": t * 0.01 + rng.standard_normal(T) * 0.1, "falling": rng.standard_normal(T) * 0.1 - t * 0.01,
+              "waves": np.round(np.sin(t / 311.0) * 40 + rng.standard_normal(T)) / 4}[kind].astype(np.float32)
+    got = _run(scores[None, None], None, s, w, k)
+    rank = oracle.ranks_from_priority(oracle.static_priority_f32(scores, 0.0))
+    np.testing.assert_array_equal(got["rank"][0, 0], rank)
+    cut = _cutoffs_by_heap(rank, s, w, k) if T > 5000 else oracle.running_cutoff_fenwick(rank, s, w, k)
+    np.testing.assert_array_equal(got["cutoff"][0, 0], cut)
+    np.testing.assert_array_equal(got["evict"][0, 0], oracle.eviction_times(rank, cut, s, w))
+    qs = sorted(set(rng.integers(0, T, 24).tolist()) | {0, min(T - 1, s + w + k - 1), T - 1})
+    y, tb = oracle.teacher_labels(rank, cut, s, w, qs)
+    np.testing.assert_array_equal(got["label"][0, 0, qs], y[qs])
+    np.testing.assert_array_equal(got["boundary"][0, 0, qs], tb[qs])
