@@ -264,9 +264,17 @@ def kvpop_future_attn_scores(q, k, lse, scale: float, window: int = 0, horizon: 
     scores = _prep_out(scores, "scores", (d.batch, d.n_kv_heads, d.seq_len), q.device)
     if out is not None or write_mass:
         out = _prep_out(out, "out", (d.batch, d.n_q_heads, d.seq_len), q.device)
+    # On a small problem with a long band the library spreads the query heads over the
+    # GPU if it can write the masses (p2_form in kvpop_kernels.hip): give it room.
+    mass, G = out, d.n_q_heads // max(1, d.n_kv_heads)
+    if (mass is None and (G - 1) * d.seq_len >= 512 and (horizon < 0 or horizon >= d.seq_len // 2)
+            and d.batch * d.n_kv_heads * ((d.seq_len + 255) // 256) < (2048 if d.head_dim == 64 or G % 2 else 1024)):
+        mass = torch.empty((d.batch, d.n_q_heads, d.seq_len), dtype=torch.float32, device=q.device)
+        if stream is not None:
+            mass.record_stream(stream)  # it is freed on return, perhaps before that stream has run
     st = lib().kvpop_future_attn_scores(ctypes.byref(d), qp, kp, bp, lse.data_ptr(), int(window), int(horizon),
                                         KVPOP_AGG_MAX if agg == "max" else KVPOP_AGG_MEAN, float(eps),
-                                        int(bool(normalize)), out.data_ptr() if out is not None else None,
+                                        int(bool(normalize)), mass.data_ptr() if mass is not None else None,
                                         scores.data_ptr(), _stream_ptr(stream, q.device))
     if st != KVPOP_OK:
         raise KvpopError(st, "kvpop_future_attn_scores")

@@ -1038,6 +1038,30 @@ future_mass_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ 
 }
 
 
+// The target epilogue as a launch of its own, after a pass 2 that spread the query heads
+// of a KV head over workgroups: one thread per (b, KV head, key) folds its G masses in
+// head order, as EPI does, and writes the same score. It reads 4 G bytes per key: 5 us at
+// B = 1, T = 4096.
+__global__ __launch_bounds__(256) void score_epilogue_kernel(const float* __restrict__ mass, float* __restrict__ scores,
+                                                             int G, int T, int window, int hz, int agg_mean, float eps,
+                                                             int normalize) {
+  const int j = (int)(blockIdx.x * 256 + threadIdx.x);
+  const size_t bh = blockIdx.y;
+  if (j >= T) return;
+  const float* m = mass + bh * G * T + j;
+  float a = 0.f;
+  for (int g = 0; g < G; ++g) {
+    const float v = m[(size_t)g * T];
+    a = agg_mean ? a + v : fmaxf(a, v);
+  }
+  float r = __logf((agg_mean ? a / (float)G : a) + eps);
+  if (normalize) {
+    const long long cnt = min((long long)T - 1, (long long)j + hz) - ((long long)j + window) + 1;
+    r -= __logf((float)max(1LL, cnt));
+  }
+  scores[bh * T + j] = r;
+}
+
 template <int D, int P, bool HB, int NQ, int NW>
 int launch_p1_q(const Launch& L) {
   constexpr int BQ = 16 * NW * NQ / P;
@@ -1140,22 +1164,67 @@ int launch_p2_b(const Launch& L, int hs) {
   return L.bias ? launch_p2<D, NSUB, GC, true, false, 1>(L, hs) : launch_p2<D, NSUB, GC, false, false, 1>(L, hs);
 }
 
-template <int D, int NSUB>
-int launch_p2_gc(const Launch& L) {
+// Pass 2's launch form: key subtiles of 16 per wave (four: 256 keys per workgroup, or two:
+// 128), and how many query heads a workgroup of a launch that spreads the heads of each
+// (key block, group) over workgroups takes (0: all of them, the sweeps stay whole). Times
+// in ms at (B, Hq/Hkv, T), D = 128 unless stated, the chosen form first:
+//  * A short single band (horizon under T / 2): two subtiles, whole sweeps. Every block
+//    does about the same work, and with two subtiles the band's edges, a large share of
+//    the steps, keep the pipelined form.
+//  * Spread while there are few groups of blocks (n = ceil(T / 256) B Hkv), since the
+//    heaviest key blocks then set the time: n = 512 (1, 32/8, 16384) 1.056 spread, 1.295
+//    whole; n = 1024 (2, 32/8, 16384) 1.939 whole, 1.969 spread. To n = 2048 with D = 64 or
+//    an odd G, whose whole sweeps take one head per step anyway (n = 1216, (4, 24/8, 9650),
+//    D = 64: 0.721 spread, 0.758 whole), and with two bands (n = 1024, (2, 32/8, 16384):
+//    2.057 spread, 2.208 whole).
+//  * Four subtiles, one head each, where that leaves 768 workgroups (three per CU), which
+//    all run well filled: 1024 (1, 32/8, 8192) 0.291 against 0.303 with two, 768
+//    (1, 32/8, 6000) 0.173 against 0.175; 512 (1, 32/8, 4096) 0.087 with two, 0.097 with four. Not
+//    for T < 4096, where the wider blocks' share of masked pairs counts ((4, 32/8, 2287):
+//    0.118 with two subtiles and two heads, 0.126 with four and one), nor for two bands,
+//    whose sums leave too few registers (n = 152, (2, 16/2, 9645), D = 64: 0.326 against 0.353):
+//    those take four subtiles from n = 512 on, and with two subtiles two heads from 512
+//    workgroups on.
+//  * With the epilogue, spreading costs an array and a launch more: not under 512 rows of
+//    extra heads ((3, 4/2, 314): 0.015 fused, 0.018 spread; (2, 6/2, 471): 0.019 spread,
+//    0.027 fused).
+struct P2Form {
+  int nsub, heads;
+};
+P2Form p2_form(const Launch& L) {
   const int G = L.Hq / L.Hkv;
-  constexpr int BK = 4 * NSUB * 16;
-  const long long grid = (long long)((L.T + BK - 1) / BK) * L.B * L.Hkv;
-  // Under 2048 workgroups (8 per CU) with a long band the heaviest key blocks set
-  // the time: the query heads of each (key block, group) are then split over
-  // several workgroups (not with the epilogue, which aggregates all G heads of a
-  // key in one workgroup). Under 512 workgroups each takes one head, else two.
-  // With a short band every block does about the same work and splitting does
-  // not pay.
-  const bool long_band = L.horizon < 0 || L.horizon >= L.T / 2 ||
-                         (L.out1 && (L.horizon1 < 0 || L.horizon1 >= L.T / 2));
-  if (!L.scores && grid < 2048 && long_band && G > 1) {
-    if (grid >= 512 && G % 2 == 0) return launch_p2_b<D, NSUB, 2>(L, G / 2);
-    return launch_p2_b<D, NSUB, 1>(L, G);
+  const long long n = (long long)((L.T + 255) / 256) * L.B * L.Hkv;
+  auto is_long = [&](int h) { return h < 0 || h >= L.T / 2; };
+  const bool long_band = is_long(L.horizon) || (L.out1 && is_long(L.horizon1));
+  if (!long_band && !L.out1) return {2, 0};
+  // The fused epilogue folds all G heads of a key in one workgroup: whole sweeps.
+  // (kvpop_future_attn_scores in the Python binding allocates the masses by these lines.)
+  const bool fused = L.scores && (!L.out || (long long)(G - 1) * L.T < 512);
+  const bool spread = long_band && !fused && G > 1 && n < (L.D == 64 || G % 2 || L.out1 ? 2048 : 1024);
+  if (!spread) return {n >= (fused || L.out1 ? 512 : 768) ? 4 : 2, 0};
+  if (!L.out1 && L.T >= 4096) return {n * G >= 768 ? 4 : 2, 1};
+  if (n >= 512) return {4, !L.out1 && G % 2 == 0 ? 2 : 1};
+  const long long grid = (long long)((L.T + 127) / 128) * L.B * L.Hkv;
+  return {2, grid >= 512 && G % 2 == 0 ? 2 : 1};
+}
+
+template <int D, int NSUB>
+int launch_p2_gc(const Launch& L, int heads) {
+  const int G = L.Hq / L.Hkv;
+  if (heads && !L.scores)
+    return heads == 2 ? launch_p2_b<D, NSUB, 2>(L, G / 2) : launch_p2_b<D, NSUB, 1>(L, G);
+  // The fused epilogue folds all G heads of a key in one workgroup, so it cannot split
+  // them; with an array for the masses the split launch and a separate epilogue are the
+  // faster pair (B = 1, 32/8 heads: T = 4096 0.172 -> 0.090 ms, T = 12345 0.70 -> 0.62 ms).
+  if (heads) {
+    Launch M = L;
+    M.scores = nullptr;
+    const int e = launch_p2_gc<D, NSUB>(M, heads);
+    if (e) return e;
+    hipLaunchKernelGGL(score_epilogue_kernel, dim3((unsigned)((L.T + 255) / 256), (unsigned)(L.B * L.Hkv)), dim3(256),
+                       0, (hipStream_t)L.stream, L.out, L.scores, G, L.T, L.window,
+                       L.horizon < 0 ? L.T : L.horizon, L.agg, L.eps, L.normalize);
+    return (int)hipGetLastError();
   }
   // Query heads per step: the largest of 4, 2, 1 that divides G.
   if (G % 4 == 0) return launch_p2_b<D, NSUB, 4>(L, 1);
@@ -1165,14 +1234,8 @@ int launch_p2_gc(const Launch& L) {
 
 template <int D>
 int launch_p2_d(const Launch& L) {
-  // Four 16-key subtiles per wave (256 keys per workgroup) unless that leaves fewer
-  // than ~2 workgroups per CU; then two (128 keys).
-  // A short single band (horizon under T / 2) also takes two: its band edges are a
-  // large share of the steps, and with two subtiles they keep the pipelined form.
-  const long long wg2 = (long long)L.B * L.Hkv * ((L.T + 255) / 256);
-  const bool short_band = L.horizon >= 0 && L.horizon < L.T / 2 && !L.out1;
-  if (wg2 >= 512 && !short_band) return launch_p2_gc<D, 4>(L);
-  return launch_p2_gc<D, 2>(L);
+  const P2Form f = p2_form(L);
+  return f.nsub == 4 ? launch_p2_gc<D, 4>(L, f.heads) : launch_p2_gc<D, 2>(L, f.heads);
 }
 
 }  // namespace

@@ -115,3 +115,36 @@ def test_scores_one_batch_row_full_length():
         m = oracle.future_mass_columns(w.q_bits[0, qh], w.k_bits[0, qh // 4], w.scale, cols)
         rel = np.abs(mass[0, qh, cols] - m) / m
         assert rel.max() <= 2e-3, "qh %d: mass max rel err %.3e" % (qh, rel.max())
+
+
+@pytest.mark.parametrize("agg", ["max", "mean"])
+@pytest.mark.parametrize("case", [
+    # B, Hq, Hkv, T, D, (window, horizon): on each side of the lines between launch forms
+    (1, 4, 2, 511, 128, (0, -1)),     # one extra head of 511 rows: fused epilogue
+    (1, 4, 2, 512, 128, (0, -1)),     # 512: heads spread, epilogue after them
+    (2, 6, 2, 300, 64, (1, 150)),     # odd group, lookahead of exactly T / 2
+    (2, 6, 2, 300, 64, (1, 149)),     # a short band: whole sweeps
+    (1, 40, 8, 4096, 64, (0, -1)),    # 640 workgroups of 256 keys and one head: 128 keys
+    (1, 48, 8, 4095, 64, (0, -1)),    # under 4096 positions: 128 keys, two heads
+    (1, 48, 8, 4096, 64, (0, -1)),    # 768 of 256 keys
+], ids=lambda c: "B%dHq%dHkv%dT%dD%d_%d_%d" % (c[:5] + c[5]))
+def test_spread_and_fused_epilogues_agree(case, agg):
+    """The same scores with and without an array for the masses, masses equal to plain
+    pass 2's bit for bit, and scores that are the epilogue of those masses to the rounding
+    of two float32 logarithms (1e-5)."""
+    B, Hq, Hkv, T, D, (win, hor) = case
+    w = workload.make(dict(seed=T + Hq, B=B, Hq=Hq, Hkv=Hkv, T=T, D=D, scale=1.0 / math.sqrt(D), kind="rope",
+                           sink=False, bands=[(0, -1)]))
+    q, k = _dev(w.q_bits), _dev(w.k_bits)
+    lse = kv.kvpop_row_lse(q, k, w.scale)
+    a, none = kv.kvpop_future_attn_scores(q, k, lse, w.scale, win, hor, agg=agg)
+    b, mass = kv.kvpop_future_attn_scores(q, k, lse, w.scale, win, hor, agg=agg, write_mass=True)
+    plain = kv.kvpop_future_attn_from_lse(q, k, lse, w.scale, win, hor)
+    assert none is None
+    np.testing.assert_array_equal(mass.cpu().numpy(), plain.cpu().numpy())
+    m = plain.cpu().numpy().astype(np.float64).reshape(B, Hkv, Hq // Hkv, T)
+    t = np.arange(T)
+    count = np.maximum(1, np.minimum(T - 1, t + (hor if hor >= 0 else T)) - (t + win) + 1)
+    ref = np.log((m.max(2) if agg == "max" else m.mean(2)) + 1e-8) - np.log(count)
+    for got in (a, b):
+        np.testing.assert_allclose(got.cpu().numpy(), ref, rtol=0, atol=1e-5)
