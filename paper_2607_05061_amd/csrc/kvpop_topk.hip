@@ -175,30 +175,32 @@ __host__ __device__ inline int census_buckets(int T) { return ((T - 1) >> census
 // ---------------------------------------------------------------------------
 // 1. Chunk sort
 // ---------------------------------------------------------------------------
-// LDS of the chunk sort, 76 KB: two workgroups share a CU. Digit d's counters of a
+// LDS of the chunk sort, 76 KB with J = 4 elements per thread: two workgroups share a CU. Digit d's counters of a
 // (slot, wave) row sit at slot(d) = 64 (d % 4) + d / 4, 16 waves side by side, so that
 // the thread that sums digit 4 lane + e reads and writes whole 16-byte rows next to its
 // neighbour lanes'.
+template <int J>
 struct SortSmem {
-  alignas(16) uint8_t cnt[kSortJ][256][kWaves];    // elements of a digit per (slot, wave): at most 64
-  alignas(16) uint16_t dst[kSortJ][256][kWaves];   // where the first of them goes
-  alignas(16) int part[kSortJ][256];               // per digit and slot
-  alignas(16) uint32_t key[kRankChunk];
-  alignas(16) uint16_t idx[kRankChunk];            // position within the chunk
-  int census[kSortJ][kSortJ];
+  alignas(16) uint8_t cnt[J][256][kWaves];         // elements of a digit per (slot, wave): at most 64
+  alignas(16) uint16_t dst[J][256][kWaves];        // where the first of them goes
+  alignas(16) int part[J][256];                    // per digit and slot
+  alignas(16) uint32_t key[J * kThreads];
+  alignas(16) uint16_t idx[J * kThreads];          // position within the chunk
+  int census[J][J];
 };
 
 // One stable counting-sort pass on the 8-bit digit at `shift`. Thread tid holds the
-// elements 1024 j + tid, j < 4, before and after. An element goes to (elements with
+// elements 1024 j + tid, j < J, before and after. An element goes to (elements with
 // smaller digits) + (elements of its digit in earlier (j, wave) rows) + (earlier lanes
 // of its wave with its digit, found with eight ballots). Bound by vector instructions,
 // about 290 per wave: 7000 cycles per pass, 16.8 us for the whole sort of up to 256 chunks
 // (28-31 us with a histogram by LDS atomics and one thread per digit's 64 counters).
-__device__ __forceinline__ void sort_pass(uint32_t (&k)[kSortJ], uint32_t (&v)[kSortJ], int shift, SortSmem& sm) {
+template <int J>
+__device__ __forceinline__ void sort_pass(uint32_t (&k)[J], uint32_t (&v)[J], int shift, SortSmem<J>& sm) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int row[kSortJ], rk[kSortJ];
+  int row[J], rk[J];
 #pragma unroll
-  for (int j = 0; j < kSortJ; ++j) {
+  for (int j = 0; j < J; ++j) {
     const uint32_t d = (k[j] >> shift) & 255u;
     uint32_t lo = ~0u, hi = ~0u;  // lanes with the same digit
 #pragma unroll
@@ -215,92 +217,101 @@ __device__ __forceinline__ void sort_pass(uint32_t (&k)[kSortJ], uint32_t (&v)[k
     if (rk[j] == 0) sm.cnt[j][row[j]][wave] = (uint8_t)(__popc(lo) + __popc(hi));
   }
   lds_barrier();
-  // Thread (e, g, lane) owns digit 4 lane + e of slot g: e = wave % 4, g = wave / 4.
+  // Thread (e, g, lane) owns digit 4 lane + e of slot g: e = wave % 4, g = wave / 4
+  // (with J < 4 slots the last waves own none).
   const int e = wave & 3, g = wave >> 2, r = 64 * e + lane;
-  const uint4 c4 = *reinterpret_cast<const uint4*>(&sm.cnt[g][r][0]);
-  *reinterpret_cast<uint4*>(&sm.cnt[g][r][0]) = uint4{0u, 0u, 0u, 0u};  // for the next pass
-  const uint32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
-  uint32_t sum = 0;
+  uint32_t c[4] = {0u, 0u, 0u, 0u};
+  if (g < J) {
+    const uint4 c4 = *reinterpret_cast<const uint4*>(&sm.cnt[g][r][0]);
+    *reinterpret_cast<uint4*>(&sm.cnt[g][r][0]) = uint4{0u, 0u, 0u, 0u};  // for the next pass
+    c[0] = c4.x, c[1] = c4.y, c[2] = c4.z, c[3] = c4.w;
+    uint32_t sum = 0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) sum = __builtin_amdgcn_sad_u8(c[i], 0u, sum);
-  sm.part[g][4 * lane + e] = (int)sum;
-  lds_barrier();
-  int p[kSortJ][4], tot = 0;
-#pragma unroll
-  for (int i = 0; i < kSortJ; ++i) {
-    const int4 x = *reinterpret_cast<const int4*>(&sm.part[i][4 * lane]);
-    p[i][0] = x.x, p[i][1] = x.y, p[i][2] = x.z, p[i][3] = x.w;
-    tot += x.x + x.y + x.z + x.w;
+    for (int i = 0; i < 4; ++i) sum = __builtin_amdgcn_sad_u8(c[i], 0u, sum);
+    sm.part[g][4 * lane + e] = (int)sum;
   }
-  int at = wave_scan<false>(tot) - tot;  // elements with digits below 4 lane
+  lds_barrier();
+  if (g < J) {
+    int p[J][4], tot = 0;
 #pragma unroll
-  for (int i = 0; i < kSortJ; ++i)
+    for (int i = 0; i < J; ++i) {
+      const int4 x = *reinterpret_cast<const int4*>(&sm.part[i][4 * lane]);
+      p[i][0] = x.x, p[i][1] = x.y, p[i][2] = x.z, p[i][3] = x.w;
+      tot += x.x + x.y + x.z + x.w;
+    }
+    int at = wave_scan<false>(tot) - tot;  // elements with digits below 4 lane
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
-      if (f < e || (f == e && i < g)) at += p[i][f];
-  uint32_t out[8];
+    for (int i = 0; i < J; ++i)
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const uint32_t a = (uint32_t)at;
-    at += (int)((c[i >> 1] >> (16 * (i & 1))) & 255u);
-    out[i] = a | ((uint32_t)at << 16);
-    at += (int)((c[i >> 1] >> (16 * (i & 1) + 8)) & 255u);
+      for (int f = 0; f < 4; ++f)
+        if (f < e || (f == e && i < g)) at += p[i][f];
+    uint32_t out[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t a = (uint32_t)at;
+      at += (int)((c[i >> 1] >> (16 * (i & 1))) & 255u);
+      out[i] = a | ((uint32_t)at << 16);
+      at += (int)((c[i >> 1] >> (16 * (i & 1) + 8)) & 255u);
+    }
+    *reinterpret_cast<uint4*>(&sm.dst[g][r][0]) = uint4{out[0], out[1], out[2], out[3]};
+    *reinterpret_cast<uint4*>(&sm.dst[g][r][8]) = uint4{out[4], out[5], out[6], out[7]};
   }
-  *reinterpret_cast<uint4*>(&sm.dst[g][r][0]) = uint4{out[0], out[1], out[2], out[3]};
-  *reinterpret_cast<uint4*>(&sm.dst[g][r][8]) = uint4{out[4], out[5], out[6], out[7]};
   lds_barrier();
 #pragma unroll
-  for (int j = 0; j < kSortJ; ++j) {
+  for (int j = 0; j < J; ++j) {
     const int d = (int)sm.dst[j][row[j]][wave] + rk[j];
     sm.key[d] = k[j];
     sm.idx[d] = (uint16_t)v[j];
   }
   lds_barrier();
 #pragma unroll
-  for (int j = 0; j < kSortJ; ++j) {
+  for (int j = 0; j < J; ++j) {
     k[j] = sm.key[j * kThreads + tid];
     v[j] = sm.idx[j * kThreads + tid];
   }
 }
 
-// One workgroup per (sequence, chunk of kRankChunk positions). Positions past T sort
+// One workgroup per (sequence, chunk of 1024 J positions): J = 4, or fewer for a sequence
+// that fits one chunk of them (J = 1: 6.1-6.8 us, J = 2: 9.6, J = 4: 15.6-17.5). Positions past T sort
 // last: they have the largest key and enter last. With a single chunk the sorted order
 // is the ranking: the kernel then writes the ranks, the positions in rank order and the
 // census itself.
+template <int J>
 __global__ __launch_bounds__(kThreads) void topk_chunk_sort_kernel(const float* __restrict__ scores,
                                                                    const float* __restrict__ log_gamma, int nseg, int H,
                                                                    int T, int s, void* ws, size_t per_seg_words,
                                                                    int32_t* __restrict__ rank) {
-  __shared__ SortSmem sm;
+  __shared__ SortSmem<J> sm;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int nch = (T + kRankChunk - 1) / kRankChunk;
+  constexpr int kChunk = J * kThreads;
+  const int nch = (T + kChunk - 1) / kChunk;
   const int c = (int)blockIdx.x / nseg, seg = (int)blockIdx.x - c * nseg;
   SegWork w = seg_work(ws, per_seg_words, seg, T);
   const float lg = log_gamma ? log_gamma[seg % H] : 0.f;
   const float* r = scores + (size_t)seg * T;
-  const int t0 = c * kRankChunk, n = min(kRankChunk, T - t0);
+  const int t0 = c * kChunk, n = min(kChunk, T - t0);
 
-  uint32_t k[kSortJ], v[kSortJ];
-  float x[kSortJ];
+  uint32_t k[J], v[J];
+  float x[J];
 #pragma unroll
-  for (int j = 0; j < kSortJ; ++j) x[j] = r[min(t0 + j * kThreads + tid, T - 1)];
+  for (int j = 0; j < J; ++j) x[j] = r[min(t0 + j * kThreads + tid, T - 1)];
 #pragma unroll
-  for (int j = 0; j < kSortJ; ++j) {
+  for (int j = 0; j < J; ++j) {
     const int i = j * kThreads + tid;
     asm volatile("" : "+v"(x[j]));  // the loads stay together, not each in a branch of its own
     k[j] = i < n ? desc_key(static_priority(x[j], (float)(t0 + i), lg)) : ~0u;
     v[j] = (uint32_t)i;
   }
-  reinterpret_cast<uint4*>(sm.cnt)[tid] = uint4{0u, 0u, 0u, 0u};
-  if (tid < kSortJ * kSortJ) (&sm.census[0][0])[tid] = 0;
+  if (tid < J * 256) reinterpret_cast<uint4*>(sm.cnt)[tid] = uint4{0u, 0u, 0u, 0u};
+  if (tid < J * J) (&sm.census[0][0])[tid] = 0;
   lds_barrier();
-  sort_pass(k, v, 0, sm);
-  sort_pass(k, v, 8, sm);
-  sort_pass(k, v, 16, sm);
-  sort_pass(k, v, 24, sm);
+  sort_pass<J>(k, v, 0, sm);
+  sort_pass<J>(k, v, 8, sm);
+  sort_pass<J>(k, v, 16, sm);
+  sort_pass<J>(k, v, 24, sm);
   if (nch > 1) {
 #pragma unroll
-    for (int j = 0; j < kSortJ; ++j) {
+    for (int j = 0; j < J; ++j) {
       const int i = j * kThreads + tid;
       if (i < n) {
         w.ka[t0 + i] = k[j];
@@ -311,22 +322,22 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_sort_kernel(const float* 
   }
   // census[block][bucket], see topk_census_kernel: slot j holds bucket j's ranks.
 #pragma unroll
-  for (int j = 0; j < kSortJ; ++j) {
+  for (int j = 0; j < J; ++j) {
     const int i = j * kThreads + tid, t = (int)v[j];
     if (i < n) {
       rank[(size_t)seg * T + t] = i;
       w.ps[i] = t;
     }
 #pragma unroll
-    for (int b = 1; b < kSortJ; ++b) {
+    for (int b = 1; b < J; ++b) {
       const int cb = __builtin_popcountll(__builtin_amdgcn_ballot_w64(i < n && t >= s && t < b * kBlock));
       if (lane == 0 && cb) atomicAdd(&sm.census[b][j], cb);
     }
   }
   lds_barrier();
   const int nb = census_buckets(T);
-  if (tid < kSortJ * kSortJ) {
-    const int blk = tid / kSortJ, b = tid - blk * kSortJ;
+  if (tid < J * J) {
+    const int blk = tid / J, b = tid - blk * J;
     if (blk < nb && b < nb) w.census[blk * nb + b] = (uint32_t)sm.census[blk][b];
   }
 }
@@ -1145,8 +1156,11 @@ int launch_running_topk(const TopkLaunch& L) {
   hipStream_t st = (hipStream_t)L.stream;
   const unsigned chunks = (unsigned)((long long)nseg * ((T + kRankChunk - 1) / kRankChunk));
   const dim3 wg(kThreads);
-  hipLaunchKernelGGL(topk_chunk_sort_kernel, dim3(chunks), wg, 0, st, L.scores, L.log_gamma, nseg, L.H, T, L.sinks,
-                     L.workspace, per, L.rank);
+  const auto sort = T <= kThreads       ? topk_chunk_sort_kernel<1>
+                    : T <= 2 * kThreads ? topk_chunk_sort_kernel<2>
+                                        : topk_chunk_sort_kernel<kSortJ>;
+  hipLaunchKernelGGL(sort, dim3(chunks), wg, 0, st, L.scores, L.log_gamma, nseg, L.H, T, L.sinks, L.workspace, per,
+                     L.rank);
   int e = (int)hipGetLastError();
   if (e) return e;
   if (T > kRankChunk) {
