@@ -1091,7 +1091,15 @@ int launch_p1_q(const Launch& L) {
 //    at once, has half the work (B = 1, T = 2048: 0.042 -> 0.031 ms);
 //  * up to two per CU: full-height blocks as 8 waves of 2 subtiles, two waves per
 //    SIMD, so that the heaviest block's MFMA and VALU work overlap even when it has
-//    its CU to itself (B = 1, T = 4096: 0.087-0.092 -> 0.084 ms).
+//    its CU to itself (B = 1, T = 4096: 0.087-0.092 -> 0.084 ms);
+//  * with P <= 2, whose blocks are tall (128 or 256 queries) and few, half-height blocks
+//    again up to 2 3/4 full-height ones per CU, and under two per CU too where the number
+//    of groups does not divide the CUs, so that heavy and light blocks are not paired: the
+//    heaviest block sets the time (B, heads, T, D: 2, 6/2, 5500, 64 0.065 -> 0.046 ms;
+//    1, 3/1, 32576, 128 0.519 -> 0.451; 3, 8/4, 5500, 64 0.087 -> 0.068). Paired 8-wave blocks
+//    stay better under two (4, 8/8, 3000, 128: 0.053 against 0.056);
+//  * from there to three per CU 8 waves (3, 12/4, 5003, 64 with a bias 0.100 -> 0.088; 2, 16/8, 6056,
+//    128 0.163 -> 0.157; 4, 8/8, 5500, 128 0.140 -> 0.134, half-height 0.139).
 template <int D, int P, bool HB>
 int launch_p1(const Launch& L) {
   const int G = L.Hq / L.Hkv;
@@ -1099,7 +1107,10 @@ int launch_p1(const Launch& L) {
   if constexpr (P < 8) {
     const int ncu = stream_cus(L.stream);
     if (grid4 <= ncu) return launch_p1_q<D, P, HB, 2, 4>(L);
-    if (grid4 <= 2LL * ncu) return launch_p1_q<D, P, HB, 2, 8>(L);
+    const bool paired = ncu > 0 && ncu % ((long long)L.B * L.Hkv * (G / P)) == 0;
+    if (grid4 <= 2LL * ncu && (P == 4 || paired)) return launch_p1_q<D, P, HB, 2, 8>(L);
+    if (P <= 2 && 4 * grid4 < 11LL * ncu) return launch_p1_q<D, P, HB, 2, 4>(L);
+    if (P <= 2 && grid4 <= 3LL * ncu) return launch_p1_q<D, P, HB, 2, 8>(L);
   }
   return launch_p1_q<D, P, HB, 4, 4>(L);
 }

@@ -113,3 +113,18 @@ def test_random_case(i):
 @pytest.mark.parametrize("c", FIXED, ids=lambda c: "B%dHq%dHkv%dT%d" % (c["B"], c["Hq"], c["Hkv"], c["T"]))
 def test_small_grid_forms(c):
     _check(c)
+
+
+PASS1_LINES = [
+    # Pass-1 launch forms of small head groups, on 256 CUs (and pass 2's beside them):
+    dict(B=3, Hq=12, Hkv=4, T=2200, D=64, bands=[(0, -1)], bias="random", seed=41),  # 324 tall blocks, unpaired
+    dict(B=4, Hq=8, Hkv=8, T=2200, D=128, bands=[(0, -1)], bias="none", seed=42),    # 288, paired: 8 waves
+    dict(B=3, Hq=8, Hkv=4, T=5500, D=64, bands=[(0, -1)], bias="none", seed=43),     # 516: half height
+    dict(B=3, Hq=12, Hkv=4, T=5003, D=64, bands=[(16, -1)], bias="random", seed=44), # 720: 8 waves
+    dict(B=3, Hq=12, Hkv=4, T=5700, D=64, bands=[(0, -1)], bias="none", seed=45),    # 828: full height
+]
+
+
+@pytest.mark.parametrize("c", PASS1_LINES, ids=lambda c: "B%dHq%dHkv%dT%d" % (c["B"], c["Hq"], c["Hkv"], c["T"]))
+def test_lines_between_pass1_forms(c):
+    _check(c)
