@@ -36,9 +36,10 @@ KERNEL_SOURCES = {
     "sparse_attn_fwd_kernel": "kvpop_sparse_attn.hip",
     "sparse_attn_fwd_kernel_exact": "kvpop_sparse_attn.hip",
     "topk_chunk_sort_kernel": "kvpop_topk.hip",
-    "topk_merge_rank_kernel": "kvpop_topk.hip",
-    "topk_prepare_kernel": "kvpop_topk.hip",
-    "topk_query_lds_kernel": "kvpop_topk.hip",
+    "topk_merge_kernel": "kvpop_topk.hip",
+    "topk_merge_runs_kernel": "kvpop_topk.hip",
+    "topk_census_kernel": "kvpop_topk.hip",
+    "topk_prepare_kernel": "kvpop_topk.hip",  # in profiles of earlier versions only
     "topk_query_kernel": "kvpop_topk.hip",
     "topk_evict_kernel": "kvpop_topk.hip",
 }
