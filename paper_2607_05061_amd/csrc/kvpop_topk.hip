@@ -25,9 +25,9 @@
 //      the eligible set only grows, so while the block's new tokens arrive the cutoff
 //      only walks down from where it stood before the block, past at most one kept
 //      token per arrival. The census gives the bucket that holds the k-th rank before
-//      the block; one scan of it finds that rank; a scan downwards from there lists the
-//      block's candidates (a few thousand at most) in rank order; and each wave then
-//      answers its 64 queries from that list.
+//      the block; one scan of it finds that rank; a scan downwards from there to the
+//      block's last cutoff lists its candidates (2048 at most) in rank order; and each
+//      wave then answers its 64 queries from that list.
 //   6. topk_evict_kernel: each token's first query with a cutoff below its rank.
 
 #include <hip/hip_runtime.h>
@@ -740,10 +740,11 @@ __global__ __launch_bounds__(kThreads) void topk_census_kernel(int nseg, int T, 
 // ---------------------------------------------------------------------------
 // 5. Queries
 // ---------------------------------------------------------------------------
-// A block of queries adds at most kBlock tokens, so its cutoffs lie within the kBlock + 1
-// largest kept ranks before it or among its own tokens; the scan that lists them stops
-// at a multiple of kBlock ranks.
-constexpr int kMaxCand = 3 * kBlock;
+// A block of queries adds at most kBlock tokens, so its last cutoff is within the kBlock + 1
+// largest ranks below the cutoff before it, and the earlier ones are not below it; the scan
+// that lists these ranks stops at a multiple of kBlock ranks, with at most kBlock entries
+// more than the kBlock it may hold before its last step.
+constexpr int kMaxCand = 2 * kBlock;
 constexpr int kMaxLocal = 192;  // a wave's own candidates: 64 + 64 kept, 64 new
 
 struct QuerySmem {
@@ -916,28 +917,29 @@ topk_query_kernel(int nseg, int T, int s, int w_win, int k, void* ws, size_t per
     if (m == 0) {  // p0 >= k here: the cutoff stays
       cut = U - 1;
     } else {
-      // Candidates: old and new ranks below U, descending, until D0 + m + 1 old ones are
-      // listed (the last query's cutoff is at or before that one) or none is left.
+      // Candidates: old and new ranks below U, descending, until D0 + m + 1 are listed. At
+      // the block's last query all of them are present, so the last one is its cutoff, and
+      // no cutoff of the block is below it (at least that many exist: k + m old and new ones
+      // once p0 >= k, p0 + m before). The blocks' scans do not overlap, so a sequence costs
+      // at most T / 1024 steps and one more per block, for any k.
       const int need = D0 + m + 1;
-      int nc = 0, nold = 0;
+      int nc = 0;
       int v = U - 1 - tid;
       int pos = v >= 0 ? w.ps[v] : -1;
-      for (int top = U; top > 0 && nold < need; top -= kThreads) {
+      for (int top = U; top > 0 && nc < need; top -= kThreads) {
         const int pv = v, pp = pos;
         v -= kThreads;
         pos = v >= 0 ? w.ps[v] : -1;  // the next step's, in flight during this one
         const bool old = pp >= s && pp < t0;
         const bool keep = old || (pp >= max(s, t0) && pp <= tl);
-        const uint64_t mo = __builtin_amdgcn_ballot_w64(old), mk = __builtin_amdgcn_ballot_w64(keep);
-        int bef, tot;
-        wave_totals<false>(__builtin_popcountll(mk) << 16 | __builtin_popcountll(mo), sm.ex, turn, bef, tot);
+        int tot;
+        const int at = block_count(keep, sm.ex, turn, tot);
         if (keep) {
-          const int i = nc + (bef >> 16) + lanes_below(mk);
+          const int i = nc + at;
           sm.cand[i] = (uint32_t)pv;
           sm.tag[i] = (uint16_t)(old ? 0 : pp - t0 + 1);
         }
-        nc += tot >> 16;
-        nold += tot & 0xFFFF;
+        nc += tot;
       }
       lds_barrier();
       // This wave's queries: D before them, and the place i0 of the cutoff there (the

@@ -234,3 +234,55 @@ def test_edges_of_blocks_chunks_and_runs(case, kind):
     y, tb = oracle.teacher_labels(rank, cut, s, w, qs)
     np.testing.assert_array_equal(got["label"][0, 0, qs], y[qs])
     np.testing.assert_array_equal(got["boundary"][0, 0, qs], tb[qs])
+
+
+@pytest.mark.parametrize("k", [1, 128, 1023, 1024, 1025])
+@pytest.mark.parametrize("kind", ["rising", "low_start", "waves"])
+def test_budgets_around_a_block_of_queries(k, kind):
+    """Budgets up to, at and above the 1024 queries of a block, with scores of which every
+    arrival is kept (rising), every arrival but the first few tokens' places (low_start: the
+    first 200 tokens outrank all later ones) or stretches (waves): the block's candidates
+    then end among its own tokens, among old ones, or span all later tokens' ranks."""
+    T, s, w = 20003, 4, 64
+    rng = np.random.default_rng(k + len(kind))
+    t = np.arange(T, dtype=np.float32)
+    scores = {"rising": t * 0.01, "low_start": t * 0.01 + 1e4 * (t < 200),
+              "waves": np.sin(t / 911.0) * 40 + rng.standard_normal(T)}[kind].astype(np.float32)
+    got = _run(scores[None, None], None, s, w, k)
+    rank = oracle.ranks_from_priority(oracle.static_priority_f32(scores, 0.0))
+    cut = _cutoffs_by_heap(rank, s, w, k)
+    np.testing.assert_array_equal(got["rank"][0, 0], rank)
+    np.testing.assert_array_equal(got["cutoff"][0, 0], cut)
+    np.testing.assert_array_equal(got["evict"][0, 0], oracle.eviction_times(rank, cut, s, w))
+    qs = sorted(set(rng.integers(0, T, 24).tolist()) | {s + w + k - 1, T - 1})
+    y, tb = oracle.teacher_labels(rank, cut, s, w, qs)
+    np.testing.assert_array_equal(got["label"][0, 0, qs], y[qs])
+    np.testing.assert_array_equal(got["boundary"][0, 0, qs], tb[qs])
+
+
+def _ms(f, n=3):
+    f()
+    best = math.inf
+    for _ in range(n):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("kind", ["rising", "low_start"])
+def test_small_budget_costs_no_more_than_a_large_one(kind):
+    """The work per query block does not grow with T where a block brings more kept tokens
+    than the budget holds: 4 million rising scores with k = 128 take about the time of
+    k = 2016 (0.33 ms; a scan past the block's last cutoff would read the whole ranking in
+    each of the 4096 blocks: 10 ms)."""
+    T = 1 << 22
+    t = torch.arange(T, device="cuda", dtype=torch.float32)
+    scores = (t * 0.01 + (1e6 * (t < 200) if kind == "low_start" else 0.0))[None, None].contiguous()
+    ws = torch.empty(kv.kvpop_running_topk_workspace_size(1, 1, T), dtype=torch.uint8, device="cuda")
+    small = _ms(lambda: kv.kvpop_running_topk(scores, 4, 64, 128, workspace=ws))
+    large = _ms(lambda: kv.kvpop_running_topk(scores, 4, 64, 2016, workspace=ws))
+    assert small <= 4 * large, "k = 128: %.3f ms, k = 2016: %.3f ms" % (small, large)
