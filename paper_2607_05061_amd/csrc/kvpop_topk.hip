@@ -853,62 +853,71 @@ topk_query_kernel(int nseg, int T, int s, int w_win, int k, void* ws, size_t per
   const int p_last = tl - s + 1;
   int cut = T, bnd = -1;
 
+  // The k-th smallest old rank, or the largest one if fewer than k are old. Before
+  // saturation it is wanted for the boundary tokens only; up to kScanOld old tokens are then
+  // scanned (a few reads in flight together, where the census takes four barriers), so that
+  // a block's work does not grow with T for any k (8 x 4194304, k = T: 6.4 ms a call, 39
+  // when every block scanned all its old tokens).
+  constexpr int kScanOld = 4 * kBlock;
+  const bool unsaturated = bnd_o && p_last >= 1 && p0 + 1 < k;  // at the block's first query
+  int old_k = INT32_MIN;
+  if (p0 >= k || (unsaturated && p0 > kScanOld)) {
+    const int kth = min(k, p0);
+    const int sh = census_shift(T), nb = census_buckets(T);
+    int cb = tid < nb ? (int)w.census[(size_t)(t0 >> sh) * nb + tid] : 0;
+    const int rest = (t0 >> sh) << sh;  // first position that the census does not count
+    if (rest < t0) {                    // only where blocks are wider than kBlock
+      sm.cnt[tid] = 0;
+      lds_barrier();
+      for (int i = max(rest, s) + tid; i < t0; i += kThreads) atomicAdd(&sm.cnt[rank[i] >> sh], 1);
+      lds_barrier();
+      cb += sm.cnt[tid];
+    }
+    // The bucket with the kth old rank: inclusive counts over the buckets.
+    const int incl = wave_scan<false>(cb);
+    int before, total;
+    wave_totals<false>(__builtin_amdgcn_readlane(incl, 63), sm.ex, turn, before, total);
+    const int upto = before + incl;
+    if (upto >= kth && upto - cb < kth) {
+      sm.found[0] = tid;
+      sm.found[1] = kth - (upto - cb);  // its place among the bucket's old ranks, from 1
+    }
+    lds_barrier();
+    int v0 = __builtin_amdgcn_readfirstlane(sm.found[0]) << sh;
+    int kk = __builtin_amdgcn_readfirstlane(sm.found[1]);
+    for (;;) {  // one round unless buckets are wider than kBlock
+      const int v = v0 + tid;
+      const int pos = v < T ? w.ps[v] : INT32_MAX;
+      const bool old = pos >= s && pos < t0;
+      int tot;
+      const int at = block_count(old, sm.ex, turn, tot);
+      if (old && at == kk - 1) sm.found[2] = v;
+      if (kk <= tot || v0 + kThreads >= T) break;
+      kk -= tot;
+      v0 += kThreads;
+    }
+    lds_barrier();
+    old_k = __builtin_amdgcn_readfirstlane(sm.found[2]);
+  }
+
   // Before saturation every eligible token is kept: the boundary token is the one with
   // the largest rank.
-  if (bnd_o && p_last >= 1 && p0 + 1 < k) {
-    int mx = elig ? r : INT32_MIN;
-    int old = INT32_MIN;
-    for (int i = s + tid; i < t0; i += kThreads) old = max(old, rank[i]);
+  if (unsaturated) {
     int before, total;
-    wave_totals<true>(__builtin_amdgcn_readlane(wave_scan<true>(old), 63), sm.ex, turn, before, total);
-    const int incl = wave_scan<true>(mx);
-    int dummy;
-    wave_totals<true>(__builtin_amdgcn_readlane(incl, 63), sm.ex, turn, before, dummy);
-    mx = max(total, max(before, incl));
+    if (p0 <= kScanOld) {
+      int old = INT32_MIN;
+      for (int i = s + tid; i < t0; i += kThreads) old = max(old, rank[i]);
+      wave_totals<true>(__builtin_amdgcn_readlane(wave_scan<true>(old), 63), sm.ex, turn, before, old_k);
+    }
+    const int incl = wave_scan<true>(elig ? r : INT32_MIN);
+    wave_totals<true>(__builtin_amdgcn_readlane(incl, 63), sm.ex, turn, before, total);
+    const int mx = max(old_k, max(before, incl));
     if (elig && p < k) bnd = w.ps[mx];
   }
 
   if (p_last >= k) {
     // U, and D before the block.
-    int U = T, D0 = p0 - k;
-    if (p0 >= k) {
-      D0 = 0;
-      const int sh = census_shift(T), nb = census_buckets(T);
-      int cb = tid < nb ? (int)w.census[(size_t)(t0 >> sh) * nb + tid] : 0;
-      const int rest = (t0 >> sh) << sh;  // first position that the census does not count
-      if (rest < t0) {                    // only where blocks are wider than kBlock
-        sm.cnt[tid] = 0;
-        lds_barrier();
-        for (int i = max(rest, s) + tid; i < t0; i += kThreads) atomicAdd(&sm.cnt[rank[i] >> sh], 1);
-        lds_barrier();
-        cb += sm.cnt[tid];
-      }
-      // The bucket with the k-th old rank: inclusive counts over the buckets.
-      const int incl = wave_scan<false>(cb);
-      int before, total;
-      wave_totals<false>(__builtin_amdgcn_readlane(incl, 63), sm.ex, turn, before, total);
-      const int upto = before + incl;
-      if (upto >= k && upto - cb < k) {
-        sm.found[0] = tid;
-        sm.found[1] = k - (upto - cb);  // its place among the bucket's old ranks, from 1
-      }
-      lds_barrier();
-      int v0 = __builtin_amdgcn_readfirstlane(sm.found[0]) << sh;
-      int kk = __builtin_amdgcn_readfirstlane(sm.found[1]);
-      for (;;) {  // one round unless buckets are wider than kBlock
-        const int v = v0 + tid;
-        const int pos = v < T ? w.ps[v] : INT32_MAX;
-        const bool old = pos >= s && pos < t0;
-        int tot;
-        const int at = block_count(old, sm.ex, turn, tot);
-        if (old && at == kk - 1) sm.found[2] = v + 1;
-        if (kk <= tot || v0 + kThreads >= T) break;
-        kk -= tot;
-        v0 += kThreads;
-      }
-      lds_barrier();
-      U = __builtin_amdgcn_readfirstlane(sm.found[2]);
-    }
+    const int U = p0 >= k ? old_k + 1 : T, D0 = p0 >= k ? 0 : p0 - k;
     // New tokens below U.
     const bool in = elig && r < U;
     const uint64_t inm = __builtin_amdgcn_ballot_w64(in);

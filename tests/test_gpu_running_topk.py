@@ -286,3 +286,38 @@ def test_small_budget_costs_no_more_than_a_large_one(kind):
     small = _ms(lambda: kv.kvpop_running_topk(scores, 4, 64, 128, workspace=ws))
     large = _ms(lambda: kv.kvpop_running_topk(scores, 4, 64, 2016, workspace=ws))
     assert small <= 4 * large, "k = 128: %.3f ms, k = 2016: %.3f ms" % (small, large)
+
+
+@pytest.mark.parametrize("case", [(5003, 0, 0, 5003), (12411, 4, 64, 9000), (12411, 4, 64, 1 << 30),
+                                  (140003, 7, 256, 140000), ((1 << 20) + 100003, 4, 64, 1 << 20)],
+                         ids=lambda c: "T%d_s%dw%dk%d" % c)
+def test_boundary_tokens_before_a_late_saturation(case):
+    """Budgets so large that most or all queries keep every eligible token: the boundary
+    token is the kept one with the largest rank, on each side of the query block from which
+    it comes from the census instead of a scan of the earlier ranks."""
+    T, s, w, k = case
+    rng = np.random.default_rng(T)
+    scores = rng.standard_normal(T).astype(np.float32)
+    got = _run(scores[None, None], None, s, w, k)
+    rank = oracle.ranks_from_priority(oracle.static_priority_f32(scores, 0.0))
+    cut = _cutoffs_by_heap(rank, s, w, k)
+    np.testing.assert_array_equal(got["cutoff"][0, 0], cut)
+    largest = np.maximum.accumulate(rank[s:T - w])  # over the eligible tokens, at query s + w + i
+    last = min(T - w - s, k - 1)                    # queries before saturation
+    at = np.empty(T, dtype=np.int64)
+    at[rank] = np.arange(T)
+    np.testing.assert_array_equal(got["boundary"][0, 0, :s + w], -1)
+    np.testing.assert_array_equal(got["boundary"][0, 0, s + w:s + w + last], at[largest[:last]])
+    np.testing.assert_array_equal(got["boundary"][0, 0, s + w + last:], at[cut[s + w + last:]])
+
+
+def test_a_budget_of_every_token_costs_no_more_than_a_large_one():
+    """The boundary tokens before saturation cost the same work per block at any T: 8
+    sequences of 4 million with k = T in about the time of k = 2016 (6.4 ms; 39 ms if each
+    block scanned all earlier ranks)."""
+    T = 1 << 22
+    scores = torch.randn(1, 8, T, device="cuda")
+    ws = torch.empty(kv.kvpop_running_topk_workspace_size(1, 8, T), dtype=torch.uint8, device="cuda")
+    full = _ms(lambda: kv.kvpop_running_topk(scores, 4, 64, T, workspace=ws))
+    large = _ms(lambda: kv.kvpop_running_topk(scores, 4, 64, 2016, workspace=ws))
+    assert full <= 4 * large, "k = T: %.3f ms, k = 2016: %.3f ms" % (full, large)
