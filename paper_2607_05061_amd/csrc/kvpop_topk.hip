@@ -820,12 +820,12 @@ __device__ __forceinline__ int local_cutoff(const uint32_t* local, uint8_t* plac
 // and by the reads' latency below that: 21.7 us for 4 x 8 x 32768 (1024 workgroups), 7.4 us
 // for 1 x 8 x 4096, against 224 and 42 us to build and walk a wavelet matrix.
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads), amdgpu_waves_per_eu(8, 8))) void
-topk_query_kernel(int nseg, int T, int s, int w_win, int k, void* ws, size_t per_seg_words,
+topk_query_kernel(int T, int s, int w_win, int k, void* ws, size_t per_seg_words,
                   const int32_t* __restrict__ ranks, int32_t* __restrict__ cutoff, int32_t* __restrict__ label,
                   int32_t* __restrict__ boundary) {
   __shared__ QuerySmem sm;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int blk = (int)blockIdx.x / nseg, seg = (int)blockIdx.x - blk * nseg;
+  const int seg = (int)blockIdx.x, blk = (int)blockIdx.y;
   SegWork w = seg_work(ws, per_seg_words, seg, T);
   const int32_t* rank = ranks + (size_t)seg * T;
   int32_t* cut_o = cutoff + (size_t)seg * T;
@@ -1188,9 +1188,12 @@ int launch_running_topk(const TopkLaunch& L) {
                        nseg, T, L.sinks, L.workspace, per);
     if ((e = (int)hipGetLastError())) return e;
   }
+  // Query blocks along y (16384 at most): a dimension holds under 2^32 work-items, and a
+  // longer one wraps without an error, which one of all blocks would from 2^21 sequences of
+  // 1025 positions on.
   const int nqb = L.window >= T ? 1 : (T - L.window + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL(topk_query_kernel, dim3((unsigned)((long long)nseg * nqb)), wg, 0, st, nseg, T, L.sinks, L.window,
-                     L.topk, L.workspace, per, L.rank, L.cutoff, L.label, L.boundary);
+  hipLaunchKernelGGL(topk_query_kernel, dim3((unsigned)nseg, (unsigned)nqb), wg, 0, st, T, L.sinks, L.window, L.topk,
+                     L.workspace, per, L.rank, L.cutoff, L.label, L.boundary);
   if ((e = (int)hipGetLastError()) || !L.evict) return e;
   hipLaunchKernelGGL(topk_evict_kernel, dim3(chunks), wg, 0, st, nseg, T, L.sinks, L.window, L.workspace, per,
                      L.cutoff, L.evict);

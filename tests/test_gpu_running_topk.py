@@ -2,6 +2,7 @@
 Sec. 3.1 eq. teacher_label). Priorities are compared in float32 on both sides (the
 ranking is an integer decided by them); ranks, cutoffs, labels and boundary tokens
 must match exactly."""
+import ctypes
 import heapq
 import math
 
@@ -321,3 +322,27 @@ def test_a_budget_of_every_token_costs_no_more_than_a_large_one():
     full = _ms(lambda: kv.kvpop_running_topk(scores, 4, 64, T, workspace=ws))
     large = _ms(lambda: kv.kvpop_running_topk(scores, 4, 64, 2016, workspace=ws))
     assert full <= 4 * large, "k = T: %.3f ms, k = 2016: %.3f ms" % (full, large)
+
+
+def test_more_than_2_pow_32_query_threads():
+    """2^21 + 64 sequences of 1025 positions, two blocks of 1024 queries each: over 2^32
+    work-items of queries. With s = w = 0 the last cutoff of every sequence is k - 1, and the
+    queries before saturation keep everything; three sequences exactly. 88 GB of memory."""
+    if torch.cuda.mem_get_info()[0] < 110e9:
+        pytest.skip("needs 110 GB of free memory")
+    n, T, k = (1 << 21) + 64, 1025, 100
+    scores = torch.randn(n, 1, T, device="cuda", generator=torch.Generator("cuda").manual_seed(9))
+    ws = torch.empty(kv.kvpop_running_topk_workspace_size(n, 1, T), dtype=torch.uint8, device="cuda")
+    rank, cut = (torch.full((n, 1, T), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+    d = kv.KvpopTopkDims(n, 1, T)
+    st = kv.lib().kvpop_running_topk(ctypes.byref(d), scores.data_ptr(), None, 0, 0, k, rank.data_ptr(),
+                                     cut.data_ptr(), None, None, None, ws.data_ptr(), ws.numel(),
+                                     torch.cuda.current_stream().cuda_stream)
+    assert st == kv.KVPOP_OK
+    assert bool((cut[..., :k - 1] == T).all()) and bool((cut[..., T - 1] == k - 1).all())
+    for i in (0, (1 << 20) + 3, n - 1):
+        e = _expected(scores[i:i + 1].cpu().numpy(), None, 0, 0, k)
+        np.testing.assert_array_equal(rank[i].cpu().numpy(), e["rank"][0])
+        np.testing.assert_array_equal(cut[i].cpu().numpy(), e["cutoff"][0])
+    del scores, ws, rank, cut
+    torch.cuda.empty_cache()
