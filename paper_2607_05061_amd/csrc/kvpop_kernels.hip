@@ -1196,6 +1196,12 @@ int launch_p2_b(const Launch& L, int hs) {
 //    whose sums leave too few registers (n = 152, (2, 16/2, 9645), D = 64: 0.326 against 0.353):
 //    those take four subtiles from n = 512 on, and with two subtiles two heads from 512
 //    workgroups on.
+//  * Whole sweeps of one query head per KV head: four subtiles from n = 704 (D = 64: 768). us,
+//    two and four subtiles: D = 128, n = 512 (4, 8/8, 3996) 70 and 93, n = 672 (2, 8/8, 10652)
+//    243 and 245, n = 704 (2, 8/8, 11164) 265 and 260, n = 768 (1, 8/8, 24476) 619 and 591;
+//    D = 64, n = 704 (1, 8/8, 22428) 358 and 365, n = 768 (1, 8/8, 24476) 421 and 424, n = 896
+//    (1, 8/8, 28572) 569 and 557. The fused epilogue takes the same form, so that its masses
+//    are plain pass 2's bit for bit (edge steps add in another order with two subtiles).
 //  * With the epilogue, spreading costs an array and a launch more: not under 512 rows of
 //    extra heads ((3, 4/2, 314): 0.015 fused, 0.018 spread; (2, 6/2, 471): 0.019 spread,
 //    0.027 fused).
@@ -1212,7 +1218,7 @@ P2Form p2_form(const Launch& L) {
   // (kvpop_future_attn_scores in the Python binding allocates the masses by these lines.)
   const bool fused = L.scores && (!L.out || (long long)(G - 1) * L.T < 512);
   const bool spread = long_band && !fused && G > 1 && n < (L.D == 64 || G % 2 || L.out1 ? 2048 : 1024);
-  if (!spread) return {n >= (fused || L.out1 ? 512 : 768) ? 4 : 2, 0};
+  if (!spread) return {n >= (G > 1 || L.out1 ? 512 : L.D == 64 ? 768 : 704) ? 4 : 2, 0};
   if (!L.out1 && L.T >= 4096) return {n * G >= 768 ? 4 : 2, 1};
   if (n >= 512) return {4, !L.out1 && G % 2 == 0 ? 2 : 1};
   const long long grid = (long long)((L.T + 127) / 128) * L.B * L.Hkv;

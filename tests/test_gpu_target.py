@@ -148,3 +148,21 @@ def test_spread_and_fused_epilogues_agree(case, agg):
     ref = np.log((m.max(2) if agg == "max" else m.mean(2)) + 1e-8) - np.log(count)
     for got in (a, b):
         np.testing.assert_allclose(got.cpu().numpy(), ref, rtol=0, atol=1e-5)
+
+
+@pytest.mark.parametrize("case", [
+    # B, H, T, D: n = ceil(T / 256) B H key blocks, on each side of 512, 704 and 768
+    (4, 8, 3800, 128), (4, 8, 4096, 128), (4, 8, 5300, 64), (4, 8, 5376, 128), (4, 8, 5500, 128), (4, 8, 5900, 64),
+    (4, 8, 6000, 64), (4, 8, 6300, 128),
+], ids=lambda c: "B%dH%dT%dD%d" % c)
+def test_masses_of_one_query_head_per_kv_head(case):
+    """G = 1: no heads to spread, so the epilogue is always fused. Its masses equal plain
+    pass 2's bit for bit, at every number of key blocks."""
+    B, H, T, D = case
+    w = workload.make(dict(seed=T, B=B, Hq=H, Hkv=H, T=T, D=D, scale=1.0 / math.sqrt(D), kind="rope", sink=False,
+                           bands=[(0, -1)]))
+    q, k = _dev(w.q_bits), _dev(w.k_bits)
+    lse = kv.kvpop_row_lse(q, k, w.scale)
+    _, mass = kv.kvpop_future_attn_scores(q, k, lse, w.scale, 0, -1, write_mass=True)
+    plain = kv.kvpop_future_attn_from_lse(q, k, lse, w.scale, 0, -1)
+    assert torch.equal(mass, plain)
