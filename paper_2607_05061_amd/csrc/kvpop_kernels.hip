@@ -1177,52 +1177,72 @@ int launch_p2_b(const Launch& L, int hs) {
 
 // Pass 2's launch form: key subtiles of 16 per wave (four: 256 keys per workgroup, or two:
 // 128), and how many query heads a workgroup of a launch that spreads the heads of each
-// (key block, group) over workgroups takes (0: all of them, the sweeps stay whole). Times
-// in ms at (B, Hq/Hkv, T), D = 128 unless stated, the chosen form first:
+// (key block, group) over workgroups takes (0: all of them, the sweeps stay whole). Medians
+// of seven runs in turn on one box, us, at (B, Hq/Hkv, T), D = 128 unless stated; runs of one
+// form differ by 1% or less up to 1 ms and by 2-4% above. n = ceil(T / 256) B Hkv.
 //  * A short single band (horizon under T / 2): two subtiles, whole sweeps. Every block
 //    does about the same work, and with two subtiles the band's edges, a large share of
 //    the steps, keep the pipelined form.
-//  * Spread while there are few groups of blocks (n = ceil(T / 256) B Hkv), since the
-//    heaviest key blocks then set the time: n = 512 (1, 32/8, 16384) 1.056 spread, 1.295
-//    whole; n = 1024 (2, 32/8, 16384) 1.939 whole, 1.969 spread. To n = 2048 with D = 64 or
-//    an odd G, whose whole sweeps take one head per step anyway (n = 1216, (4, 24/8, 9650),
-//    D = 64: 0.721 spread, 0.758 whole), and with two bands (n = 1024, (2, 32/8, 16384):
-//    2.057 spread, 2.208 whole).
-//  * Four subtiles, one head each, where that leaves 768 workgroups (three per CU), which
-//    all run well filled: 1024 (1, 32/8, 8192) 0.291 against 0.303 with two, 768
-//    (1, 32/8, 6000) 0.173 against 0.175; 512 (1, 32/8, 4096) 0.087 with two, 0.097 with four. Not
-//    for T < 4096, where the wider blocks' share of masked pairs counts ((4, 32/8, 2287):
-//    0.118 with two subtiles and two heads, 0.126 with four and one), nor for two bands,
-//    whose sums leave too few registers (n = 152, (2, 16/2, 9645), D = 64: 0.326 against 0.353):
-//    those take four subtiles from n = 512 on, and with two subtiles two heads from 512
-//    workgroups on.
-//  * Whole sweeps of one query head per KV head: four subtiles from n = 704 (D = 64: 768). us,
-//    two and four subtiles: D = 128, n = 512 (4, 8/8, 3996) 70 and 93, n = 672 (2, 8/8, 10652)
+//  * Otherwise the heaviest key blocks set the time while there are few blocks, and the
+//    heads are spread under n = 2048.
+//    - n >= 1024: two heads per workgroup ((4, 32/8, 15500) D = 64: 2403, one head 2451; (16,
+//      32/8, 2287) 399, whole sweeps 436), but whole sweeps, whose steps take four heads, with
+//      D = 128, G % 4 = 0 and 5120 or more (block, head) pairs n G ((3, 32/8, 16384) 3160, two
+//      heads 3252; (8, 64/8, 4000) 1120 and 1175). D = 64, G = 2: one head, as two are the
+//      whole sweep ((4, 16/8, 8192) 351 and 369). Odd G: one head, as in its whole sweeps
+//      ((4, 24/8, 9650) D = 64: 728 and 759; equal at n = 1536).
+//    - n >= 512, T >= 4096: four subtiles, one head ((1, 32/8, 28672) 3100, two heads and
+//      whole sweeps 3257; (4, 32/8, 4096) D = 64: 199, two heads 205; D = 128: 278 and 280).
+//    - n < 512, T >= 4096: four subtiles and one head where the pairs fill the CUs, three
+//      workgroups each, and the sweeps are long, so that the wider blocks' masked pairs count
+//      little. From T = 8192 on that is 768 pairs ((1, 16/8, 12288), 768: 309, two subtiles
+//      318), with D = 64, whose steps have half the MFMA work, 1024 ((1, 32/8, 8192), 1024:
+//      189 and 194; (1, 12/4, 16384), 768: 291 and 287). Below T = 8192, with D = 128, 1152 ((2,
+//      32/8, 5000), 1280: 208 and 215; (2, 32/8, 4300), 1088: 160 and 155), and never with D = 64
+//      ((2, 32/8, 5000) 157 and 144). Otherwise two subtiles, with two heads from 896 pairs on
+//      ((4, 16/4, 4096), 1024: 137, one head 145; (3, 16/8, 4096), 768: 119 and 115).
+//    - T < 4096, and two bands with n < 512, whose sums leave too few registers for four
+//      subtiles: two subtiles, two heads from 512 workgroups of 128 keys on ((4, 32/8, 2287)
+//      97, one head 105, four subtiles 110). T < 4096, n >= 512: four subtiles, two heads.
+//    - Two bands, n >= 512: four subtiles, one head, and two from 4608 pairs on ((4, 32/8,
+//      12288) 2531, one head 2580; (2, 32/8, 12288), 3072: 1268 and 1221), with G = 2 from 3584
+//      on ((4, 16/8, 15000) 1759 and 1801; (4, 16/8, 12288), 3072: 1246 and 1195).
+//  * Whole sweeps of one query head per KV head: four subtiles from n = 704 (D = 64: 768).
+//    Two and four subtiles: D = 128, n = 512 (4, 8/8, 3996) 70 and 93, n = 672 (2, 8/8, 10652)
 //    243 and 245, n = 704 (2, 8/8, 11164) 265 and 260, n = 768 (1, 8/8, 24476) 619 and 591;
 //    D = 64, n = 704 (1, 8/8, 22428) 358 and 365, n = 768 (1, 8/8, 24476) 421 and 424, n = 896
 //    (1, 8/8, 28572) 569 and 557. The fused epilogue takes the same form, so that its masses
 //    are plain pass 2's bit for bit (edge steps add in another order with two subtiles).
 //  * With the epilogue, spreading costs an array and a launch more: not under 512 rows of
-//    extra heads ((3, 4/2, 314): 0.015 fused, 0.018 spread; (2, 6/2, 471): 0.019 spread,
-//    0.027 fused).
+//    extra heads ((3, 4/2, 314): 15 fused, 18 spread; (2, 6/2, 471): 19 spread, 27 fused).
 struct P2Form {
-  int nsub, heads;
+  int nsub, heads;  // heads: 1 or 2, fewer than G
 };
 P2Form p2_form(const Launch& L) {
-  const int G = L.Hq / L.Hkv;
-  const long long n = (long long)((L.T + 255) / 256) * L.B * L.Hkv;
-  auto is_long = [&](int h) { return h < 0 || h >= L.T / 2; };
-  const bool long_band = is_long(L.horizon) || (L.out1 && is_long(L.horizon1));
-  if (!long_band && !L.out1) return {2, 0};
+  const int G = L.Hq / L.Hkv, T = L.T;
+  const bool two = L.out1 != nullptr, even = G % 2 == 0, d64 = L.D == 64;
+  const long long n = (long long)((T + 255) / 256) * L.B * L.Hkv, pairs = n * G;
+  auto is_long = [&](int h) { return h < 0 || h >= T / 2; };
+  const bool long_band = is_long(L.horizon) || (two && is_long(L.horizon1));
+  if (!long_band && !two) return {2, 0};
   // The fused epilogue folds all G heads of a key in one workgroup: whole sweeps.
   // (kvpop_future_attn_scores in the Python binding allocates the masses by these lines.)
-  const bool fused = L.scores && (!L.out || (long long)(G - 1) * L.T < 512);
-  const bool spread = long_band && !fused && G > 1 && n < (L.D == 64 || G % 2 || L.out1 ? 2048 : 1024);
-  if (!spread) return {n >= (G > 1 || L.out1 ? 512 : L.D == 64 ? 768 : 704) ? 4 : 2, 0};
-  if (!L.out1 && L.T >= 4096) return {n * G >= 768 ? 4 : 2, 1};
-  if (n >= 512) return {4, !L.out1 && G % 2 == 0 ? 2 : 1};
-  const long long grid = (long long)((L.T + 127) / 128) * L.B * L.Hkv;
-  return {2, grid >= 512 && G % 2 == 0 ? 2 : 1};
+  const bool fused = L.scores && (!L.out || (long long)(G - 1) * T < 512);
+  const bool wide = !two && n >= 1024 && !d64 && G % 4 == 0 && pairs >= 5120;
+  if (!long_band || fused || G == 1 || n >= 2048 || wide)
+    return {n >= (G > 1 || two ? 512 : d64 ? 768 : 704) ? 4 : 2, 0};
+  const int heads2 = !even ? 1 : G == 2 ? 0 : 2;  // two heads where G allows: all of them if G = 2
+  if (n >= 512) {
+    const bool pair = two ? pairs >= (G == 2 ? 3584 : 4608) : T < 4096 || (n >= 1024 && !(d64 && G == 2));
+    return {4, pair ? heads2 : 1};
+  }
+  if (two || T < 4096) {
+    const long long grid = (long long)((T + 127) / 128) * L.B * L.Hkv;
+    return {2, grid >= 512 ? heads2 : 1};
+  }
+  const bool four = T >= 8192 ? pairs >= (d64 ? 1024 : 768) : !d64 && pairs >= 1152;
+  if (four) return {4, 1};
+  return {2, pairs >= 896 ? heads2 : 1};
 }
 
 template <int D, int NSUB>

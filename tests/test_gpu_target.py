@@ -4,6 +4,7 @@ scores[b, h, t] = log(agg_g m_bar + eps) - log N_t is compared in absolute terms
 a 2e-3 relative error on the masses is at most ~2e-3 on their logarithm, so the bar
 is |gpu - oracle| <= 2e-3 (+ 1e-5 for the fp32 logarithm itself).
 """
+import ctypes
 import math
 
 import numpy as np
@@ -103,10 +104,9 @@ def test_scores_full_size_sampled():
 
 
 def test_scores_one_batch_row_full_length():
-    """B = 1, T = 32768: plain pass 2 spreads each key block's query heads over two
-    workgroups, the fused launch keeps them in one. Both sum each key's terms in the
-    same order (bit for bit), and keys of the last key blocks match the oracle's
-    columns."""
+    """B = 1, T = 32768: plain pass 2 and the scores' call with an array for the masses
+    spread each key block's query heads over two workgroups, in one form (masses bit for
+    bit), and keys of the last key blocks match the oracle's columns."""
     w = workload.make("qwen3_8b_t32k", B=1)
     _, out, mass = _scores(w, 0, -1, "mean", 1e-8, True, write_mass=True)
     np.testing.assert_array_equal(out, mass)
@@ -117,37 +117,82 @@ def test_scores_one_batch_row_full_length():
         assert rel.max() <= 2e-3, "qh %d: mass max rel err %.3e" % (qh, rel.max())
 
 
+FORMS = [
+    # B, Hq, Hkv, T, D, (window, horizon): on each side of the lines between pass 2's launch
+    # forms (key subtiles per wave, query heads per workgroup; 0: whole sweeps); n = ceil(T / 256)
+    # B Hkv blocks, n G pairs
+    (1, 4, 2, 511, 128, (0, -1)),      # one extra head of 511 rows: fused epilogue, 2 / 0
+    (1, 4, 2, 512, 128, (0, -1)),      # 512: heads spread, epilogue after them, 2 / 1
+    (2, 6, 2, 300, 64, (1, 150)),      # odd group, lookahead of exactly T / 2: 2 / 1
+    (2, 6, 2, 300, 64, (1, 149)),      # a short band: 2 / 0
+    (4, 32, 8, 2287, 128, (0, -1)),    # under 4096 positions, n = 288, 576 workgroups: 2 / 2
+    (4, 32, 8, 1900, 64, (0, -1)),     # n = 256, 480 workgroups: 2 / 1
+    (8, 32, 8, 2100, 64, (0, -1)),     # n = 576: 4 / 2
+    (8, 16, 8, 2100, 128, (0, -1)),    # n = 576, two heads are all: 4 / 0
+    (1, 48, 8, 4096, 64, (0, -1)),     # 4096 positions, 768 pairs: 2 / 1
+    (2, 32, 8, 4096, 128, (0, -1)),    # n = 256, 1024 pairs: 2 / 2
+    (2, 32, 8, 4600, 128, (0, -1)),    # 1152 pairs: 4 / 1
+    (2, 32, 8, 4600, 64, (0, -1)),     # D = 64: 2 / 2
+    (4, 24, 4, 4300, 64, (0, -1)),     # G = 6: 2 / 2
+    (1, 16, 8, 8191, 128, (0, -1)),    # n = 256, 512 pairs: 2 / 1
+    (1, 24, 8, 8192, 128, (0, -1)),    # 768 pairs: 4 / 1
+    (1, 32, 8, 7900, 64, (0, -1)),     # 992 pairs below 8192 positions: 2 / 2
+    (1, 32, 8, 8192, 64, (0, -1)),     # 1024 pairs: 4 / 1
+    (4, 32, 8, 4096, 64, (0, -1)),     # n = 512: 4 / 1
+    (8, 32, 8, 4096, 128, (0, -1)),    # n = 1024, 4096 pairs: 4 / 2
+    (8, 64, 8, 3900, 128, (0, -1)),    # n = 1024, 8192 pairs: 4 / 0
+    (8, 16, 8, 4096, 64, (0, -1)),     # n = 1024, G = 2, D = 64: 4 / 1
+]
+
+
+def _scores_without_masses(q, k, lse, scale, win, hor, agg, bias):
+    """kvpop_future_attn_scores with out = NULL: always the fused epilogue."""
+    B, Hq, T, D = q.shape
+    d = kv.KvpopDims(B, Hq, k.shape[1], T, D, float(scale))
+    sc = torch.full((B, k.shape[1], T), float("nan"), device="cuda")
+    st = kv.lib().kvpop_future_attn_scores(
+        ctypes.byref(d), q.data_ptr(), k.data_ptr(), bias.data_ptr() if bias is not None else None, lse.data_ptr(), win,
+        hor, kv.KVPOP_AGG_MAX if agg == "max" else kv.KVPOP_AGG_MEAN, 1e-8, 1, None, sc.data_ptr(),
+        torch.cuda.current_stream().cuda_stream)
+    assert st == kv.KVPOP_OK
+    return sc
+
+
 @pytest.mark.parametrize("agg", ["max", "mean"])
-@pytest.mark.parametrize("case", [
-    # B, Hq, Hkv, T, D, (window, horizon): on each side of the lines between launch forms
-    (1, 4, 2, 511, 128, (0, -1)),     # one extra head of 511 rows: fused epilogue
-    (1, 4, 2, 512, 128, (0, -1)),     # 512: heads spread, epilogue after them
-    (2, 6, 2, 300, 64, (1, 150)),     # odd group, lookahead of exactly T / 2
-    (2, 6, 2, 300, 64, (1, 149)),     # a short band: whole sweeps
-    (1, 40, 8, 4096, 64, (0, -1)),    # 640 workgroups of 256 keys and one head: 128 keys
-    (1, 48, 8, 4095, 64, (0, -1)),    # under 4096 positions: 128 keys, two heads
-    (1, 48, 8, 4096, 64, (0, -1)),    # 768 of 256 keys
-], ids=lambda c: "B%dHq%dHkv%dT%dD%d_%d_%d" % (c[:5] + c[5]))
-def test_spread_and_fused_epilogues_agree(case, agg):
-    """The same scores with and without an array for the masses, masses equal to plain
-    pass 2's bit for bit, and scores that are the epilogue of those masses to the rounding
-    of two float32 logarithms (1e-5)."""
+@pytest.mark.parametrize("biased", [False, True], ids=["plain", "biased"])
+@pytest.mark.parametrize("case", FORMS, ids=lambda c: "B%dHq%dHkv%dT%dD%d_%d_%d" % (c[:5] + c[5]))
+def test_spread_and_fused_epilogues_agree(case, biased, agg):
+    """The epilogue fused into pass 2 (the C entry without an array for the masses), and the
+    binding's call with and without masses: masses equal to plain pass 2's bit for bit, and
+    scores that are the epilogue of those masses to the rounding of two float32 logarithms
+    (1e-5) and, fused, of sums of up to T terms in another order (T 2^-24 at most, their
+    square root in practice: 1e-5 too). Biased: keys at -inf, mass 0, and one at -40, whose
+    block takes the exact sweep."""
     B, Hq, Hkv, T, D, (win, hor) = case
-    w = workload.make(dict(seed=T + Hq, B=B, Hq=Hq, Hkv=Hkv, T=T, D=D, scale=1.0 / math.sqrt(D), kind="rope",
+    w = workload.make(dict(seed=T + Hq, B=1, Hq=Hq, Hkv=Hkv, T=T, D=D, scale=1.0 / math.sqrt(D), kind="rope",
                            sink=False, bands=[(0, -1)]))
-    q, k = _dev(w.q_bits), _dev(w.k_bits)
-    lse = kv.kvpop_row_lse(q, k, w.scale)
-    a, none = kv.kvpop_future_attn_scores(q, k, lse, w.scale, win, hor, agg=agg)
-    b, mass = kv.kvpop_future_attn_scores(q, k, lse, w.scale, win, hor, agg=agg, write_mass=True)
-    plain = kv.kvpop_future_attn_from_lse(q, k, lse, w.scale, win, hor)
+    q, k = (_dev(x).expand(B, -1, -1, -1).contiguous() for x in (w.q_bits, w.k_bits))
+    bias = None
+    if biased:
+        bias = torch.zeros(T, device="cuda")
+        bias[5::97] = -math.inf
+        bias[T // 3] = -40.0
+    lse = kv.kvpop_row_lse(q, k, w.scale, key_bias=bias)
+    a, none = kv.kvpop_future_attn_scores(q, k, lse, w.scale, win, hor, agg=agg, key_bias=bias)
+    b, mass = kv.kvpop_future_attn_scores(q, k, lse, w.scale, win, hor, agg=agg, key_bias=bias, write_mass=True)
+    fused = _scores_without_masses(q, k, lse, w.scale, win, hor, agg, bias)
+    plain = kv.kvpop_future_attn_from_lse(q, k, lse, w.scale, win, hor, key_bias=bias)
     assert none is None
-    np.testing.assert_array_equal(mass.cpu().numpy(), plain.cpu().numpy())
-    m = plain.cpu().numpy().astype(np.float64).reshape(B, Hkv, Hq // Hkv, T)
-    t = np.arange(T)
-    count = np.maximum(1, np.minimum(T - 1, t + (hor if hor >= 0 else T)) - (t + win) + 1)
-    ref = np.log((m.max(2) if agg == "max" else m.mean(2)) + 1e-8) - np.log(count)
-    for got in (a, b):
-        np.testing.assert_allclose(got.cpu().numpy(), ref, rtol=0, atol=1e-5)
+    assert torch.equal(mass, plain)
+    if biased:
+        assert bool((plain[..., 5::97] == 0).all())
+    m = plain.double().view(B, Hkv, Hq // Hkv, T)
+    t = torch.arange(T, device="cuda")
+    count = ((t + (hor if hor >= 0 else T)).clamp(max=T - 1) - (t + win) + 1).clamp(min=1)
+    ref = ((m.amax(2) if agg == "max" else m.mean(2)) + 1e-8).log() - count.double().log()
+    for what, got in (("binding", a), ("with masses", b), ("fused", fused)):
+        err = (got.double() - ref).abs().max().item()
+        assert err <= 2e-5, "%s: %.2e" % (what, err)
 
 
 @pytest.mark.parametrize("case", [
