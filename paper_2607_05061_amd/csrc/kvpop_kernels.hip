@@ -1093,24 +1093,34 @@ int launch_p1_q(const Launch& L) {
 //    SIMD, so that the heaviest block's MFMA and VALU work overlap even when it has
 //    its CU to itself (B = 1, T = 4096: 0.087-0.092 -> 0.084 ms);
 //  * with P <= 2, whose blocks are tall (128 or 256 queries) and few, half-height blocks
-//    again up to 2 3/4 full-height ones per CU, and under two per CU too where the number
-//    of groups does not divide the CUs, so that heavy and light blocks are not paired: the
-//    heaviest block sets the time (B, heads, T, D: 2, 6/2, 5500, 64 0.065 -> 0.046 ms;
-//    1, 3/1, 32576, 128 0.519 -> 0.451; 3, 8/4, 5500, 64 0.087 -> 0.068). Paired 8-wave blocks
-//    stay better under two (4, 8/8, 3000, 128: 0.053 against 0.056);
-//  * from there to three per CU 8 waves (3, 12/4, 5003, 64 with a bias 0.100 -> 0.088; 2, 16/8, 6056,
-//    128 0.163 -> 0.157; 4, 8/8, 5500, 128 0.140 -> 0.134, half-height 0.139).
+//    further on, also under two per CU where the number of groups does not divide the CUs, so
+//    that heavy and light blocks are not paired: the heaviest block sets the time (us at (B,
+//    Hq/Hkv, T): (2, 6/2, 5771) D = 64 57, 8 waves 75, full height 83; paired 8-wave blocks stay
+//    better: (4, 8/8, 3979) 72, half height 84). They stop paying at 2 1/4 blocks per CU with P =
+//    1 and D = 128 ((3, 12/4, 3979), 2.25: 93.0, full height 93.6; (3, 12/4, 4235), 2.39: 104 and
+//    101; (2, 6/2, 14475), 2.67: 345 and 324), at 2 1/2 with P = 2 ((3, 8/4, 6411), 2.39: 139 and
+//    144; (2, 16/8, 5259), 2.62: 127 and 123) or D = 64 with a bias ((2, 8/8, 9611), 2.38: 152 and
+//    158; (1, 9/9, 18059), 2.5: 295 and 289), at 2 3/4 with D = 64 and none ((2, 8/8, 10635),
+//    2.62: 164 and 173) or P = 2 ((3, 8/4, 7307) with a bias, 2.72: 127 and 127);
+//  * from 2 3/4 to three per CU 8 waves ((4, 8/8, 5515) 135, full height 140; (3, 12/4, 5003) 126
+//    and 136, D = 64 with a bias 92 and 102), with D = 128 the later the longer the sequence, as
+//    full-height blocks feed four MFMAs per K fragment instead of two: from 2 7/8 for T = 8192
+//    ((2, 8/8, 11403), 2.81: 268 and 265; (2, 8/8, 11659), 2.88: 276 and 278; D = 64 184 and 187),
+//    only at three for 16384 ((1, 9/9, 21131), 2.92: 500 and 490), never from 24576 on.
 template <int D, int P, bool HB>
 int launch_p1(const Launch& L) {
   const int G = L.Hq / L.Hkv;
   const long long grid4 = (long long)((L.T + 256 / P - 1) / (256 / P)) * L.B * L.Hkv * (G / P);
   if constexpr (P < 8) {
-    const int ncu = stream_cus(L.stream);
+    const long long ncu = stream_cus(L.stream);
     if (grid4 <= ncu) return launch_p1_q<D, P, HB, 2, 4>(L);
     const bool paired = ncu > 0 && ncu % ((long long)L.B * L.Hkv * (G / P)) == 0;
-    if (grid4 <= 2LL * ncu && (P == 4 || paired)) return launch_p1_q<D, P, HB, 2, 8>(L);
-    if (P <= 2 && 4 * grid4 < 11LL * ncu) return launch_p1_q<D, P, HB, 2, 4>(L);
-    if (P <= 2 && grid4 <= 3LL * ncu) return launch_p1_q<D, P, HB, 2, 8>(L);
+    if (grid4 <= 2 * ncu && (P == 4 || paired)) return launch_p1_q<D, P, HB, 2, 8>(L);
+    if constexpr (P <= 2) {
+      constexpr int quarters = (D == 128 ? 9 : HB ? 10 : 11) + (P == 2 && (D == 128 || HB) ? 1 : 0);
+      if (4 * grid4 < quarters * ncu) return launch_p1_q<D, P, HB, 2, 4>(L);
+      if (8 * grid4 >= (22 + (D == 128 ? L.T / 8192 : 0)) * ncu && grid4 <= 3 * ncu) return launch_p1_q<D, P, HB, 2, 8>(L);
+    }
   }
   return launch_p1_q<D, P, HB, 4, 4>(L);
 }

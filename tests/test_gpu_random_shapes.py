@@ -120,6 +120,10 @@ PASS1_LINES = [
     dict(B=3, Hq=12, Hkv=4, T=2200, D=64, bands=[(0, -1)], bias="random", seed=41),  # 324 tall blocks, unpaired
     dict(B=4, Hq=8, Hkv=8, T=2200, D=128, bands=[(0, -1)], bias="none", seed=42),    # 288, paired: 8 waves
     dict(B=3, Hq=8, Hkv=4, T=5500, D=64, bands=[(0, -1)], bias="none", seed=43),     # 516: half height
+    dict(B=3, Hq=12, Hkv=4, T=4300, D=128, bands=[(0, -1)], bias="none", seed=46),   # 612, D = 128: full height
+    dict(B=3, Hq=12, Hkv=4, T=4300, D=64, bands=[(0, -1)], bias="random", seed=47),  # 612, D = 64: half height
+    dict(B=3, Hq=8, Hkv=4, T=6400, D=128, bands=[(0, -1)], bias="none", seed=48),    # 600, P = 2: half height
+    dict(B=3, Hq=12, Hkv=4, T=4700, D=64, bands=[(0, -1)], bias="random", seed=49),  # 684 with a bias: full height
     dict(B=3, Hq=12, Hkv=4, T=5003, D=64, bands=[(16, -1)], bias="random", seed=44), # 720: 8 waves
     dict(B=3, Hq=12, Hkv=4, T=5700, D=64, bands=[(0, -1)], bias="none", seed=45),    # 828: full height
 ]
