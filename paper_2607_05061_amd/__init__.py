@@ -2,9 +2,14 @@
 
 A thin ctypes binding over the in-tree ``libkvpop.so`` (C ABI in ``include/kvpop.h``).
 Every function here only marshals arguments: it checks tensor placement, dtype and
-layout, derives the dimensions, allocates outputs with PyTorch when the caller
-passes none, and calls the C entry point of the same name on the current HIP
-stream. All arithmetic runs in the library's HIP kernels; there is no fallback.
+layout, derives the dimensions, allocates with PyTorch the outputs (and scratch) that
+the caller does not pass, and calls the C entry point of the same name on the current
+HIP stream or on ``stream``. All arithmetic runs in the library's HIP kernels; there is
+no fallback.
+
+Outputs that a call allocates belong to the current stream, as every torch result does;
+a caller that passes another ``stream`` orders the two streams itself, or passes outputs.
+Scratch comes from the memory of the stream that the kernels run on.
 
 Quantities (KVpop App. D.1): for query head qh and key position t,
 
@@ -16,6 +21,7 @@ with query head qh reading KV head qh // (Hq // Hkv); horizon < 0 = no limit.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 from typing import Optional, Tuple
@@ -155,6 +161,21 @@ def _stream_ptr(stream, device) -> int:
     return int(s.cuda_stream)
 
 
+def _on_launch_stream(stream, device):
+    """A context with the stream that the kernels run on as torch's current one: scratch that
+    a call drops on return is allocated in it, so that the caching allocator orders the work
+    before and after the call on that memory. ``stream`` is any object with a handle."""
+    torch = _torch()
+    if stream is None:
+        if device.index == torch.cuda.current_device():
+            return contextlib.nullcontext()
+        stream = torch.cuda.current_stream(device)
+    elif not isinstance(stream, torch.cuda.Stream):
+        h = int(stream.cuda_stream)
+        stream = torch.cuda.ExternalStream(h, device=device) if h else torch.cuda.default_stream(device)
+    return torch.cuda.stream(stream)
+
+
 def _prep_inputs(q, k, key_bias):
     torch = _torch()
     _check_tensor(q, "q", torch.bfloat16, None)
@@ -252,7 +273,10 @@ def kvpop_future_attn_scores(q, k, lse, scale: float, window: int = 0, horizon: 
                              write_mass: bool = False, stream=None):
     """Pass 2 plus the target epilogue (App. D.4 step 5): per-KV-head scores
     log(agg_g m_bar + eps) - log N_t, fp32 [B, Hkv, T]. Returns (scores, out), where
-    out holds the per-head masses if ``write_mass`` (or ``out``) is given, else None."""
+    out holds the per-head masses if ``write_mass`` (or ``out``) is given, else None.
+    Where that is faster the masses get an array of their own for the time of the call
+    (B * Hq * T floats), but not while the stream is being captured: a captured call takes
+    the faster form only with ``write_mass`` or ``out``."""
     torch = _torch()
     d = _dims(q, k, scale)
     qp, kp, bp = _prep_inputs(q, k, key_bias)
@@ -265,13 +289,14 @@ def kvpop_future_attn_scores(q, k, lse, scale: float, window: int = 0, horizon: 
     if out is not None or write_mass:
         out = _prep_out(out, "out", (d.batch, d.n_q_heads, d.seq_len), q.device)
     # On a small problem with a long band the library spreads the query heads over the
-    # GPU if it can write the masses (p2_form in kvpop_kernels.hip): give it room.
+    # GPU if it can write the masses (p2_form in kvpop_kernels.hip): give it room, except
+    # under capture, whose replays would write to it after it is freed.
     mass, G = out, d.n_q_heads // max(1, d.n_kv_heads)
     if (mass is None and (G - 1) * d.seq_len >= 512 and (horizon < 0 or horizon >= d.seq_len // 2)
             and d.batch * d.n_kv_heads * ((d.seq_len + 255) // 256) < (2048 if d.head_dim == 64 or G % 2 else 1024)):
-        mass = torch.empty((d.batch, d.n_q_heads, d.seq_len), dtype=torch.float32, device=q.device)
-        if stream is not None:
-            mass.record_stream(stream)  # it is freed on return, perhaps before that stream has run
+        with _on_launch_stream(stream, q.device):
+            if not torch.cuda.is_current_stream_capturing():
+                mass = torch.empty((d.batch, d.n_q_heads, d.seq_len), dtype=torch.float32, device=q.device)
     st = lib().kvpop_future_attn_scores(ctypes.byref(d), qp, kp, bp, lse.data_ptr(), int(window), int(horizon),
                                         KVPOP_AGG_MAX if agg == "max" else KVPOP_AGG_MEAN, float(eps),
                                         int(bool(normalize)), mass.data_ptr() if mass is not None else None,
