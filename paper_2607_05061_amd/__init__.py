@@ -329,7 +329,8 @@ def kvpop_running_topk(scores, sinks: int, window: int, topk: int, log_gamma=Non
     if need == 0:
         raise ValueError("invalid dimensions")
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=scores.device)
+        with contextlib.nullcontext() if stream is None else _on_launch_stream(stream, scores.device):
+            workspace = torch.empty(need, dtype=torch.uint8, device=scores.device)
     elif workspace.numel() * workspace.element_size() < need or workspace.device != scores.device:
         raise ValueError("workspace must hold %d bytes on the device of scores" % need)
     out = {n: torch.empty((B, H, T), dtype=torch.int32, device=scores.device) for n in ("rank", "cutoff")}

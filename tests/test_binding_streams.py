@@ -3,7 +3,6 @@ drops (no GPU: torch's allocator and streams, and the library, are stand-ins tha
 The caching allocator orders a block's reuse on the stream that was current when it was
 allocated, so such an array has to come from the stream that the kernels run on."""
 import contextlib
-import ctypes
 import types
 
 import pytest
@@ -149,3 +148,16 @@ def test_masses_the_caller_asks_for_are_returned(monkeypatch):
     w = _World(monkeypatch, capturing=True)
     allocated, out, mass = w.scores_call(w.side, write_mass=True)
     assert allocated == [mass] and out == mass.data_ptr()
+
+
+@pytest.mark.parametrize("explicit", [True, False])
+def test_top_k_workspace_comes_from_the_launch_stream(monkeypatch, explicit):
+    w = _World(monkeypatch)
+    r = w.given((1, 8, 4096), "f32")
+    out = kv.kvpop_running_topk(r, 4, 256, 2016, stream=w.side if explicit else None)
+    (name, args), = w.calls
+    assert name == "kvpop_running_topk"
+    scratch = [t for t in w.allocated if all(t is not o for o in out.values())]
+    assert [t.pool for t in scratch] == [w.side if explicit else w.main]
+    assert args[11] == scratch[0].data_ptr() and args[12] == scratch[0].numel()
+    assert all(o.pool is w.main for o in out.values())

@@ -47,3 +47,37 @@ def test_side_stream_matches_default_stream(explicit):
     assert set(got) == set(ref)
     for name in ref:
         assert torch.equal(got[name], ref[name]), name
+
+
+class _Handle:
+    """A stream that is not torch's: only its handle."""
+
+    def __init__(self, s):
+        self.cuda_stream = s.cuda_stream
+
+
+@pytest.mark.parametrize("wrap", [lambda s: s, _Handle], ids=["stream", "handle"])
+def test_explicit_stream_beside_another_current_one(wrap):
+    """The stream is passed while another one is current, which allocates and writes memory
+    right after each call returns: scratch that the calls dropped is not handed to it."""
+    w = workload.make(dict(seed=56, B=1, Hq=32, Hkv=8, T=4096, D=128, scale=1 / math.sqrt(128), kind="rope",
+                           sink=True, bands=[(0, -1)]))
+    q, k = _dev(w.q_bits), _dev(w.k_bits)
+    bias = torch.from_numpy(w.bias).to("cuda")
+    lse = kv.kvpop_row_lse(q, k, w.scale, key_bias=bias)
+    ref, _ = kv.kvpop_future_attn_scores(q, k, lse, w.scale, 0, -1, key_bias=bias)
+    ref_tk = kv.kvpop_running_topk(ref, 4, 256, 2016, evict=True)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for _ in range(4):
+        scores = torch.empty_like(ref)
+        side.wait_stream(torch.cuda.current_stream())
+        kv.kvpop_future_attn_scores(q, k, lse, w.scale, 0, -1, key_bias=bias, scores=scores, stream=wrap(side))
+        noise = [torch.full((1, 32, 4096), float("nan"), device="cuda") for _ in range(3)]
+        tk = kv.kvpop_running_topk(scores, 4, 256, 2016, evict=True, stream=wrap(side))
+        noise += [torch.full((1 << 19,), float("nan"), device="cuda") for _ in range(4)]
+        torch.cuda.synchronize()
+        assert torch.equal(scores, ref)
+        for n in ref_tk:
+            assert torch.equal(tk[n], ref_tk[n]), n
+        del noise
