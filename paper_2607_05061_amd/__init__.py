@@ -97,6 +97,8 @@ def lib() -> ctypes.CDLL:
         L.kvpop_future_attn_target.restype = ctypes.c_int
         L.kvpop_future_attn_scores.argtypes = [D, P, P, P, P, I32, I32, I32, F, I32, P, P, P]
         L.kvpop_future_attn_scores.restype = ctypes.c_int
+        L.kvpop_internal_scores_spread.argtypes = [D, I32, I32]
+        L.kvpop_internal_scores_spread.restype = ctypes.c_int
         L.kvpop_running_topk_workspace_size.argtypes = [ctypes.POINTER(KvpopTopkDims)]
         L.kvpop_running_topk_workspace_size.restype = ctypes.c_size_t
         L.kvpop_running_topk.argtypes = [ctypes.POINTER(KvpopTopkDims), P, P, I32, I32, I32, P, P, P, P, P, P,
@@ -289,11 +291,10 @@ def kvpop_future_attn_scores(q, k, lse, scale: float, window: int = 0, horizon: 
     if out is not None or write_mass:
         out = _prep_out(out, "out", (d.batch, d.n_q_heads, d.seq_len), q.device)
     # On a small problem with a long band the library spreads the query heads over the
-    # GPU if it can write the masses (p2_form in kvpop_kernels.hip): give it room, except
-    # under capture, whose replays would write to it after it is freed.
-    mass, G = out, d.n_q_heads // max(1, d.n_kv_heads)
-    if (mass is None and (G - 1) * d.seq_len >= 512 and (horizon < 0 or horizon >= d.seq_len // 2)
-            and d.batch * d.n_kv_heads * ((d.seq_len + 255) // 256) < (2048 if d.head_dim == 64 or G % 2 else 1024)):
+    # GPU if it can write the masses: give it room, except under capture, whose replays
+    # would write to it after it is freed.
+    mass = out
+    if mass is None and lib().kvpop_internal_scores_spread(ctypes.byref(d), int(window), int(horizon)):
         with _on_launch_stream(stream, q.device):
             if not torch.cuda.is_current_stream_capturing():
                 mass = torch.empty((d.batch, d.n_q_heads, d.seq_len), dtype=torch.float32, device=q.device)

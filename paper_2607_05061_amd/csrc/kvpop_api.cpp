@@ -285,6 +285,15 @@ int kvpop_future_attn_scores(const kvpop_dims* dims, const void* q, const void* 
   return launch([&] { return kvpop::launch_future_mass(L); });
 }
 
+int kvpop_internal_scores_spread(const kvpop_dims* dims, int32_t window, int32_t horizon) {
+  Sizes sz;
+  if (check_dims(dims, &sz) != KVPOP_OK || check_band(window, horizon) != KVPOP_OK) return 0;
+  kvpop::Launch L = make_launch(dims, nullptr, nullptr, nullptr, nullptr);
+  L.window = window;
+  L.horizon = horizon;
+  return kvpop::scores_spread(L) ? 1 : 0;
+}
+
 size_t kvpop_running_topk_workspace_size(const kvpop_topk_dims* d) {
   if (!d || d->batch < 1 || d->n_heads < 1 || d->seq_len < 1 || d->seq_len > KVPOP_MAX_SEQ_LEN) return 0;
   const size_t seqs = (size_t)d->batch * (size_t)d->n_heads;

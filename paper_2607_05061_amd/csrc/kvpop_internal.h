@@ -68,6 +68,9 @@ void sparse_attn_plan(SparseLaunch& L);
 // Each returns 0 on success or the hipError_t of a failed launch.
 int launch_row_lse(const Launch& L);
 int launch_future_mass(const Launch& L);
+// Whether kvpop_future_attn_scores on these sizes and band spreads the query heads over
+// workgroups when it has an array for the masses (which is then the faster form).
+bool scores_spread(Launch L);
 int launch_running_topk(const TopkLaunch& L);
 int launch_sparse_attn_fwd(SparseLaunch L);
 size_t topk_workspace_words_per_seq(int T);
@@ -78,3 +81,7 @@ int stream_cus(void* stream);
 int noalloc_scratch(void* stream, void** ptr);
 
 }  // namespace kvpop
+
+// scores_spread for the Python binding, which then allocates the masses: 1 or 0 (also for
+// arguments that kvpop_future_attn_scores rejects). Launches nothing.
+extern "C" int kvpop_internal_scores_spread(const struct kvpop_dims* dims, int32_t window, int32_t horizon);

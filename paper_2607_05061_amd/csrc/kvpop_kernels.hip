@@ -1225,6 +1225,7 @@ int launch_p2_b(const Launch& L, int hs) {
 //    are plain pass 2's bit for bit (edge steps add in another order with two subtiles).
 //  * With the epilogue, spreading costs an array and a launch more: not under 512 rows of
 //    extra heads ((3, 4/2, 314): 15 fused, 18 spread; (2, 6/2, 471): 19 spread, 27 fused).
+constexpr int kSpreadRows = 512;
 struct P2Form {
   int nsub, heads;  // heads: 1 or 2, fewer than G
 };
@@ -1236,8 +1237,7 @@ P2Form p2_form(const Launch& L) {
   const bool long_band = is_long(L.horizon) || (two && is_long(L.horizon1));
   if (!long_band && !two) return {2, 0};
   // The fused epilogue folds all G heads of a key in one workgroup: whole sweeps.
-  // (kvpop_future_attn_scores in the Python binding allocates the masses by these lines.)
-  const bool fused = L.scores && (!L.out || (long long)(G - 1) * T < 512);
+  const bool fused = L.scores && (!L.out || (long long)(G - 1) * T < kSpreadRows);
   const bool wide = !two && n >= 1024 && !d64 && G % 4 == 0 && pairs >= 5120;
   if (!long_band || fused || G == 1 || n >= 2048 || wide)
     return {n >= (G > 1 || two ? 512 : d64 ? 768 : 704) ? 4 : 2, 0};
@@ -1305,6 +1305,11 @@ int stream_cus(void* stream) {
 int launch_row_lse(const Launch& L) {
   if (L.D == 64) return launch_p1_d<64>(L);
   return launch_p1_d<128>(L);
+}
+
+bool scores_spread(Launch L) {
+  L.scores = nullptr;
+  return (long long)(L.Hq / L.Hkv - 1) * L.T >= kSpreadRows && p2_form(L).heads != 0;
 }
 
 int launch_future_mass(const Launch& L) {

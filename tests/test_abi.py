@@ -314,3 +314,19 @@ def test_forced_hip_error_path(monkeypatch):
     assert err.status == kv.KVPOP_EHIP and "HIP error: " in str(err)
     monkeypatch.delenv("KVPOP_TEST_FORCE_EHIP")
     assert _lse(_dims(B=0)) == EINVAL
+
+
+def test_scores_spread_rule():
+    """Where the binding gives kvpop_future_attn_scores an array for the masses: small
+    problems with several query heads per KV head and a long band."""
+    f = kv.lib().kvpop_internal_scores_spread
+
+    def spread(B, Hq, Hkv, T, D, w=0, h=-1):
+        return f(ctypes.byref(_dims(B, Hq, Hkv, T, D)), w, h)
+
+    assert spread(1, 4, 2, 512, 128) == 1 and spread(1, 4, 2, 511, 128) == 0      # 512 rows of extra heads
+    assert spread(2, 6, 2, 300, 64, 1, 150) == 1 and spread(2, 6, 2, 300, 64, 1, 149) == 0  # a band of T / 2
+    assert spread(1, 32, 8, 4096, 128) == 1 and spread(4, 8, 8, 4096, 128) == 0   # G = 1
+    assert spread(4, 32, 8, 16384, 128) == 0 and spread(1, 32, 8, 16384, 128) == 1
+    assert spread(4, 24, 8, 16383, 64) == 0 and spread(4, 24, 8, 16128, 64) == 1  # n = 2048, 2016
+    assert f(None, 0, -1) == 0 and spread(1, 5, 2, 4096, 128) == 0 and spread(1, 4, 2, 4096, 128, 3, 2) == 0
