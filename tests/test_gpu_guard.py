@@ -6,10 +6,13 @@ sweep and return the mass itself: within the relative 2e-3 bar of the fp64 oracl
 +inf exactly where the mass exceeds the fp32 range, 0 for keys biased -inf, and
 never NaN.
 
-The cases run three launch forms: kvpop_future_attn_from_lse on a small grid (the
-query heads of each key block spread over several workgroups), the same on a grid
-of 2048 workgroups or more (every head in one workgroup), and
-kvpop_future_attn_scores with its per-head masses (the fused epilogue's launch)."""
+The cases run these launch forms: kvpop_future_attn_from_lse on a small grid (the
+query heads of each key block spread over several workgroups) and on 2048 blocks of 256
+keys or more (every head in one workgroup), kvpop_future_attn_scores with its per-head
+masses (spread like the former with a long band, the fused epilogue's launch with a short
+one), and the same through the C ABI without masses (always the fused epilogue), whose
+scores are checked."""
+import ctypes
 import math
 
 import numpy as np
@@ -56,11 +59,41 @@ def _check(got, ref, window, what):
     return int(over.sum())
 
 
-def _run_all(w, lse, bias, window, horizon):
-    """Masses from the small-grid (head-split) launch and from the fused-epilogue launch."""
+def _fused_scores(q, k, lse, scale, window, horizon, bias):
+    """Scores (max over heads, eps 1e-8, normalised) of the fused epilogue: out = NULL."""
+    B, Hq, T, D = q.shape
+    d = kv.KvpopDims(B, Hq, k.shape[1], T, D, float(scale))
+    sc = torch.full((B, k.shape[1], T), float("nan"), device="cuda")
+    st = kv.lib().kvpop_future_attn_scores(
+        ctypes.byref(d), q.data_ptr(), k.data_ptr(), bias.data_ptr() if bias is not None else None, lse.data_ptr(),
+        window, horizon, kv.KVPOP_AGG_MAX, 1e-8, 1, None, sc.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert st == kv.KVPOP_OK
+    torch.cuda.synchronize()
+    return sc.cpu().numpy().astype(np.float64)
+
+
+def _check_scores(got, ref, window, horizon, what):
+    """got: scores [B, Hkv, T]; ref: fp64 oracle masses [B, Hq, T]. A relative error of REL on the
+    masses is at most that on the logarithm, plus 1e-5 of the fp32 logarithm itself."""
+    B, Hkv, T = got.shape
+    m = ref.reshape(B, Hkv, -1, T).max(axis=2)
+    t = np.arange(T)
+    count = np.maximum(1, np.minimum(T - 1, t + (horizon if horizon >= 0 else T)) - (t + window) + 1)
+    assert not np.isnan(got).any(), what + ": NaN"
+    over = m > FLT_MAX * (1 + REL)
+    ok = m < FLT_MAX * (1 - REL)
+    assert np.all(np.isposinf(got[over])), what + ": masses beyond the fp32 range"
+    err = np.abs(got - (np.log(np.where(ok, m, 1.0) + 1e-8) - np.log(count)))[ok]
+    assert err.max() <= REL + 1e-5, "%s: max abs err %.3e" % (what, err.max())
+
+
+def _run_all(w, lse, bias, window, horizon, ref):
+    """Masses from the small-grid (head-split) launch and from the scores' launch with masses;
+    the fused epilogue's scores are checked here."""
     q, k = _dev(w.q_bits), _dev(w.k_bits)
     b = _f32(bias) if bias is not None else None
     lse_d = _f32(lse)
+    _check_scores(_fused_scores(q, k, lse_d, w.scale, window, horizon, b), ref, window, horizon, "fused epilogue")
     split = kv.kvpop_future_attn_from_lse(q, k, lse_d, w.scale, window, horizon, key_bias=b)
     _, epi = kv.kvpop_future_attn_scores(q, k, lse_d, w.scale, window, horizon, agg="max", eps=1e-8, key_bias=b,
                                          write_mass=True)
@@ -83,9 +116,9 @@ def test_normaliser_80_below_on_some_rows(band):
     lse32 = lse.astype(np.float32)
     ref = oracle.future_mass(w.q_bits, w.k_bits, w.scale, w.bias, *band, lse=lse32.astype(np.float64))
     assert ref.max() > 2.0 ** 64
-    split, epi = _run_all(w, lse32, w.bias, *band)
+    split, epi = _run_all(w, lse32, w.bias, *band, ref)
     _check(split, ref, band[0], "split")
-    _check(epi, ref, band[0], "epilogue launch")
+    _check(epi, ref, band[0], "scores with masses")
 
 
 def test_normaliser_100_below_gives_inf():
@@ -100,9 +133,9 @@ def test_normaliser_100_below_gives_inf():
     lse[:, :, 400] -= 100.0
     lse32 = lse.astype(np.float32)
     ref = oracle.future_mass(w.q_bits, w.k_bits, w.scale, bias, 0, -1, lse=lse32.astype(np.float64))
-    split, epi = _run_all(w, lse32, bias, 0, -1)
+    split, epi = _run_all(w, lse32, bias, 0, -1, ref)
     assert _check(split, ref, 0, "split") > 100
-    _check(epi, ref, 0, "epilogue launch")
+    _check(epi, ref, 0, "scores with masses")
     assert np.all(split[..., 5::37] == 0.0) and np.all(epi[..., 5::37] == 0.0)
 
 
@@ -127,9 +160,9 @@ def test_evicted_heavy_key():
     logits = oracle.causal_logits(w.q_bits[0, 0], w.k_bits[0, 0], w.scale)
     assert np.min(logits[jstar:, jstar] - np.max(np.where(mask, logits, -np.inf)[jstar:], axis=1)) > 60
     assert np.all(ref[..., jstar] > FLT_MAX * 2)
-    split, epi = _run_all(w, lse32, None, 0, -1)
+    split, epi = _run_all(w, lse32, None, 0, -1, ref)
     _check(split, ref, 0, "split")
-    _check(epi, ref, 0, "epilogue launch")
+    _check(epi, ref, 0, "scores with masses")
     assert np.all(np.isposinf(split[..., jstar]))
 
 
@@ -150,19 +183,22 @@ def test_bias_minus_80_on_a_dominant_key(T):
     qd, kd, bd = _dev(w.q_bits), _dev(w.k_bits), _f32(bias)
     out, lse = kv.kvpop_future_attn_target(qd, kd, w.scale, 0, -1, key_bias=bd)
     _, epi = kv.kvpop_future_attn_scores(qd, kd, lse, w.scale, 0, -1, key_bias=bd, write_mass=True)
-    torch.cuda.synchronize()
+    fused = _fused_scores(qd, kd, lse, w.scale, 0, -1, bd)
     out = out.cpu().numpy().astype(np.float64)
     epi = epi.cpu().numpy().astype(np.float64)
     lse = lse.cpu().numpy().astype(np.float64)
-    for g in (0, 3):
+    refs = {}
+    for g in range(4):
         lse_ref = oracle.row_lse_blocked(w.q_bits[0, g], w.k_bits[0, 0], w.scale, bias, threads=8)
         assert np.abs(lse[0, g] - lse_ref).max() <= 5e-4
         ref = oracle.future_mass_blocked(w.q_bits[0, g], w.k_bits[0, 0], w.scale, bias, 0, -1, lse=lse_ref,
                                          threads=8)
+        refs[g] = ref
         assert ref[jstar] > 0.5 * (T - jstar)  # the key takes most of every later row
         _check(out[0, g][None], ref[None], 0, "target head %d" % g)
-        _check(epi[0, g][None], ref[None], 0, "epilogue head %d" % g)
+        _check(epi[0, g][None], ref[None], 0, "scores with masses, head %d" % g)
     np.testing.assert_allclose(out.sum(axis=-1), T, rtol=REL)
+    _check_scores(fused, np.stack([refs[g] for g in range(4)])[None], 0, -1, "fused epilogue")
 
 
 def test_bias_plus_100():
@@ -175,14 +211,14 @@ def test_bias_plus_100():
     bias[450] = 100.0
     lse = oracle.row_lse(w.q_bits, w.k_bits, w.scale, bias)
     ref = oracle.future_mass(w.q_bits, w.k_bits, w.scale, bias, 0, -1, lse=lse)
-    split, epi = _run_all(w, lse.astype(np.float32), bias, 0, -1)
+    split, epi = _run_all(w, lse.astype(np.float32), bias, 0, -1, ref)
     _check(split, ref, 0, "split")
-    _check(epi, ref, 0, "epilogue launch")
+    _check(epi, ref, 0, "scores with masses")
     np.testing.assert_allclose(split[..., 450], T - 450, rtol=REL)
 
 
 def test_unsplit_launch_with_lowered_normaliser():
-    """A grid of 2048 workgroups (not split) with LSE_d lowered by 85 on a few rows of
+    """2048 blocks of 256 keys (not split) with LSE_d lowered by 85 on a few rows of
     every head, and by 100 on one row of one head."""
     B, H, T, D = 8, 8, 8192, 64
     w = workload.make(dict(seed=506, B=B, Hq=H, Hkv=H, T=T, D=D, scale=1.0 / math.sqrt(D), kind="rope",
