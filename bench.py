@@ -33,13 +33,13 @@ CSRC = os.path.join(ROOT, "paper_2607_05061_amd", "csrc")
 KERNEL_SOURCES = {
     "row_lse_kernel": "kvpop_kernels.hip",
     "future_mass_kernel": "kvpop_kernels.hip",
+    "score_epilogue_kernel": "kvpop_kernels.hip",
     "sparse_attn_fwd_kernel": "kvpop_sparse_attn.hip",
     "sparse_attn_fwd_kernel_exact": "kvpop_sparse_attn.hip",
     "topk_chunk_sort_kernel": "kvpop_topk.hip",
     "topk_merge_kernel": "kvpop_topk.hip",
     "topk_merge_runs_kernel": "kvpop_topk.hip",
     "topk_census_kernel": "kvpop_topk.hip",
-    "topk_prepare_kernel": "kvpop_topk.hip",  # in profiles of earlier versions only
     "topk_query_kernel": "kvpop_topk.hip",
     "topk_evict_kernel": "kvpop_topk.hip",
 }

@@ -3,6 +3,7 @@ of profiled kernel names, the lookup of recorded HBM traffic by source hash, and
 refusal of more than one GPU."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -43,8 +44,21 @@ def test_kernel_key():
         "sparse_attn_fwd_kernel_exact"
     assert bench.kernel_key(ns + "future_mass_kernel<128, 2, 4, false, true>(...)") == "future_mass_kernel"
     assert bench.kernel_key(ns + "row_lse_kernel<128, 4, false>(...)") == "row_lse_kernel"
-    assert bench.kernel_key("kvpop::topk_prepare_kernel(...)") == "topk_prepare_kernel"
+    assert bench.kernel_key(ns + "score_epilogue_kernel(...)") == "score_epilogue_kernel"
+    for name in ("topk_chunk_sort_kernel<4>", "topk_merge_kernel<true>", "topk_merge_runs_kernel", "topk_census_kernel",
+                 "topk_query_kernel", "topk_evict_kernel"):
+        assert bench.kernel_key("void %s%s(int, int)" % (ns, name)) == name.split("<")[0]
     assert bench.kernel_key("__amd_rocclr_copyBuffer") is None
+
+
+def test_profiled_kernels_are_those_of_the_sources():
+    """Every kernel of the sources is in the list under its file, and no other."""
+    found = {}
+    for f in sorted(set(bench.KERNEL_SOURCES.values())):
+        for name in re.findall(r"\b(\w+_kernel)\(", open(os.path.join(bench.CSRC, f)).read()):
+            found[name] = f
+    listed = {k: f for k, f in bench.KERNEL_SOURCES.items() if not k.endswith("_exact")}
+    assert listed == found
 
 
 def test_traffic_lookup_follows_the_source_hash(tmp_path, monkeypatch):

@@ -156,7 +156,7 @@ def test_long_context_t131072():
 
 
 @pytest.mark.parametrize("T", [32771, 32772, 40000, 136072])
-def test_each_wavelet_build(T):
+def test_ragged_chunks_and_runs(T):
     """Several sorted chunks of 4096 positions, the last one of 3, 4 or 3136 (T = 32771,
     32772, 40000), and two runs of chunks, the second of 5000 positions (T = 136072).
     Ranks, cutoffs and eviction queries of every position exactly, labels and boundaries
@@ -175,10 +175,10 @@ def test_each_wavelet_build(T):
         np.testing.assert_array_equal(got["boundary"][0, h, qs], e["boundary"][0, 0, qs])
 
 
-def test_queries_from_lds_ragged_length():
+def test_many_sequences_of_ragged_length():
     """64 sequences of T = 12411 (a ragged last block of queries, and more workgroups of
-    queries than the chip holds at once). Ranks, cutoffs and eviction queries of three sequences exactly, labels and
-    boundaries on sampled queries."""
+    queries than the chip holds at once). Ranks, cutoffs and eviction queries of three
+    sequences exactly, labels and boundaries on sampled queries."""
     B, H, T, s, w, k = 8, 8, 12411, 4, 256, 2016
     rng = np.random.default_rng(77)
     scores = rng.standard_normal((B, H, T)).astype(np.float32)
