@@ -21,7 +21,6 @@ with query head qh reading KV head qh // (Hq // Hkv); horizon < 0 = no limit.
 """
 from __future__ import annotations
 
-import contextlib
 import ctypes
 import os
 from typing import Optional, Tuple
@@ -169,8 +168,6 @@ def _on_launch_stream(stream, device):
     before and after the call on that memory. ``stream`` is any object with a handle."""
     torch = _torch()
     if stream is None:
-        if device.index == torch.cuda.current_device():
-            return contextlib.nullcontext()
         stream = torch.cuda.current_stream(device)
     elif not isinstance(stream, torch.cuda.Stream):
         h = int(stream.cuda_stream)
@@ -293,15 +290,19 @@ def kvpop_future_attn_scores(q, k, lse, scale: float, window: int = 0, horizon: 
     # On a small problem with a long band the library spreads the query heads over the
     # GPU if it can write the masses: give it room, except under capture, whose replays
     # would write to it after it is freed.
-    mass = out
-    if mass is None and lib().kvpop_internal_scores_spread(ctypes.byref(d), int(window), int(horizon)):
-        with _on_launch_stream(stream, q.device):
+    mass, L, dims = out, lib(), ctypes.byref(d)
+    if mass is None and L.kvpop_internal_scores_spread(dims, int(window), int(horizon)):
+        if stream is None and q.device.index == torch.cuda.current_device():  # no context: a small call's time is host time
             if not torch.cuda.is_current_stream_capturing():
-                mass = torch.empty((d.batch, d.n_q_heads, d.seq_len), dtype=torch.float32, device=q.device)
-    st = lib().kvpop_future_attn_scores(ctypes.byref(d), qp, kp, bp, lse.data_ptr(), int(window), int(horizon),
-                                        KVPOP_AGG_MAX if agg == "max" else KVPOP_AGG_MEAN, float(eps),
-                                        int(bool(normalize)), mass.data_ptr() if mass is not None else None,
-                                        scores.data_ptr(), _stream_ptr(stream, q.device))
+                mass = torch.empty(lse.shape, dtype=torch.float32, device=q.device)
+        else:
+            with _on_launch_stream(stream, q.device):
+                if not torch.cuda.is_current_stream_capturing():
+                    mass = torch.empty(lse.shape, dtype=torch.float32, device=q.device)
+    st = L.kvpop_future_attn_scores(dims, qp, kp, bp, lse.data_ptr(), int(window), int(horizon),
+                                    KVPOP_AGG_MAX if agg == "max" else KVPOP_AGG_MEAN, float(eps),
+                                    int(bool(normalize)), mass.data_ptr() if mass is not None else None,
+                                    scores.data_ptr(), _stream_ptr(stream, q.device))
     if st != KVPOP_OK:
         raise KvpopError(st, "kvpop_future_attn_scores")
     return scores, out
@@ -330,8 +331,11 @@ def kvpop_running_topk(scores, sinks: int, window: int, topk: int, log_gamma=Non
     if need == 0:
         raise ValueError("invalid dimensions")
     if workspace is None:
-        with contextlib.nullcontext() if stream is None else _on_launch_stream(stream, scores.device):
+        if stream is None:
             workspace = torch.empty(need, dtype=torch.uint8, device=scores.device)
+        else:
+            with _on_launch_stream(stream, scores.device):
+                workspace = torch.empty(need, dtype=torch.uint8, device=scores.device)
     elif workspace.numel() * workspace.element_size() < need or workspace.device != scores.device:
         raise ValueError("workspace must hold %d bytes on the device of scores" % need)
     out = {n: torch.empty((B, H, T), dtype=torch.int32, device=scores.device) for n in ("rank", "cutoff")}
